@@ -208,9 +208,24 @@ __device__ __forceinline__ void tile_slots(const TG &g, int x0, int y0, int (&vu
   }
 }
 
-// The buffers a tiled kernel reads (rnull: an empty buffer, every load 0).
+// The arrays a tiled kernel reads.  A plane outside the box (or past the
+// chunk) is read through a descriptor of 0 bytes, so that every load of a step
+// is issued without a branch: with one descriptor or another chosen per load
+// the compiler branched around the loads of f and waited for the first of them
+// (s_waitcnt vmcnt(0)) before it issued those of u and psi, two memory round
+// trips per plane step instead of one.  Isolated launches at 257^3 / 129^3,
+// before -> now: FP64 residual 382 -> 342 / 54.9 -> 49.2 us, residual norm 303
+// -> 277 / 49.9 -> 46.0 us, FP32 residual 228 -> 213 / 35.8 -> 34.5 us; the
+// FP64 half-sweep stays at 335 / 41 us (bound by the 1.67 GB it moves).
 struct TileBufs {
-  __amdgpu_buffer_rsrc_t u, f, psi, out, null;
+  const void *u, *f, *psi;
+  int vbytes, pbytes;
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t ru(bool in) const {
+    return make_rsrc(u, in ? vbytes : 0);
+  }
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rp(bool in) const {
+    return make_rsrc(psi, in ? pbytes : 0);
+  }
 };
 
 template <typename T>
@@ -228,18 +243,16 @@ __device__ __forceinline__ void tile_put_p(T *slot, const T (&rp)[NPCT]) {
 template <typename T>
 __device__ __forceinline__ void tile_fetch_u(const TG &g, const TileBufs &B, const int (&vu)[NUPT],
                                              int z, T (&ru)[NUPT]) {
-  const bool zin = z >= 0 && z < g.nz;
-  const __amdgpu_buffer_rsrc_t r1 = zin ? B.u : B.null;
-  const int so = zin ? z * g.nx * g.ny * (int)sizeof(T) : 0;
+  const __amdgpu_buffer_rsrc_t r1 = B.ru(z >= 0 && z < g.nz);
+  const int so = z * g.nx * g.ny * (int)sizeof(T);
 #pragma unroll
   for (int j = 0; j < NUPT; ++j) ru[j] = bload<T>(r1, vu[j], so);
 }
 template <typename T>
 __device__ __forceinline__ void tile_fetch_p(const TG &g, const TileBufs &B, const int (&vp)[NPCT],
                                              int zc, T (&rp)[NPCT]) {
-  const bool zin = zc >= 0 && zc < g.cz;
-  const __amdgpu_buffer_rsrc_t r2 = zin ? B.psi : B.null;
-  const int sq = zin ? zc * g.cx * g.cy * (int)sizeof(T) : 0;
+  const __amdgpu_buffer_rsrc_t r2 = B.rp(zc >= 0 && zc < g.cz);
+  const int sq = zc * g.cx * g.cy * (int)sizeof(T);
 #pragma unroll
   for (int j = 0; j < NPCT; ++j) rp[j] = bload<T>(r2, vp[j], sq);
 }
@@ -390,8 +403,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   constexpr int W = sizeof(T);
   const int nn = g.nn, nxy = g.nx * g.ny;
   const int vbytes = 3 * nn * W;
-  const TileBufs B{make_rsrc(u, vbytes), make_rsrc(f, vbytes), make_rsrc(psi, g.cx * g.cy * g.cz * W),
-                   make_rsrc(u_out, vbytes), make_rsrc(u, 0)};
+  const TileBufs B{u, f, psi, vbytes, g.cx * g.cy * g.cz * W};
+  const __amdgpu_buffer_rsrc_t rout = make_rsrc(u_out, vbytes);
   const int tx = lt % tg.ntx, rest = lt / tg.ntx;
   const int ty = rest % tg.nty, tz = rest / tg.nty;
   const int x0 = tx * TX, y0 = ty * TY;
@@ -410,23 +423,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   // DotSrc)
   constexpr bool R64 = DOT && sizeof(T) == 4;
   using FT = std::conditional_t<R64, double, T>;
-  const __amdgpu_buffer_rsrc_t rr = make_rsrc(R64 ? (const void *)ds.r : (const void *)f,
-                                              R64 ? 3 * nn * 8 : vbytes);
   const int fw = R64 ? 8 / W : 1;  // FP64 offsets from FP32 ones
   const double sn = R64 ? sqrt(*ds.ss) : 0.0;
   auto fetch_f = [&](int k, FT (&r)[3], FT (&rc)[3]) __attribute__((always_inline)) {
-    const bool ok = k < k1;
-    const __amdgpu_buffer_rsrc_t rf = ok ? (R64 ? rr : B.f) : B.null;
+    const __amdgpu_buffer_rsrc_t rf = make_rsrc(R64 ? (const void *)ds.r : B.f,
+                                                k < k1 ? vbytes * fw : 0);
     const int vo = ((pg + k) & 1) ? vn1 : vn0;
-    const int so = ok ? k * nxy * W * fw : 0;
+    const int so = k * nxy * W * fw;
     const int vof = vo == kOOB ? kOOB : vo * fw;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) r[c] = bload<FT>(rf, vof, so + (ok ? c * nn * W * fw : 0));
+    for (int c = 0; c < 3; ++c) r[c] = bload<FT>(rf, vof, so + c * nn * W * fw);
     if constexpr (DOT) {
       const int vc = ((pg + k) & 1) ? vn0 : vn1;
       const int vcf = vc == kOOB ? kOOB : vc * fw;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) rc[c] = bload<FT>(rf, vcf, so + (ok ? c * nn * W * fw : 0));
+      for (int c = 0; c < 3; ++c) rc[c] = bload<FT>(rf, vcf, so + c * nn * W * fw);
     }
   };
   // MASK: the class of the updated node of plane k, loaded a plane ahead too
@@ -447,7 +458,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   T RU[NUPT], RP[NPCT];
   for (int k = k0; k < k1; ++k) {
     const int clk = CLN;
-    CLN = fetch_cls(k + 1);
     T fv[3];
     FT fc[3], fr[3];
 #pragma unroll
@@ -460,9 +470,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
       }
       if (DOT) fc[c] = FC[c];
     }
-    fetch_f(k + 1, FN, FC);
     tile_fetch_u<T>(g, B, vu, k + 2, RU);
     tile_fetch_p<T>(g, B, vp, k + 1, RP);
+    fetch_f(k + 1, FN, FC);
+    CLN = fetch_cls(k + 1);
     const T *Lm = su[(k + 2) % 3], *L0 = su[k % 3], *L1 = su[(k + 1) % 3];
     const T *Pm = sp[(k + 1) & 1], *P0 = sp[k & 1];
     const int par = (pg + k) & 1;
@@ -493,8 +504,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     const int vo_u = par ? vn1 : vn0, vo_c = par ? vn0 : vn1;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      bstore<T>(nv[c], B.out, vo_u, so + c * nn * W);
-      bstore<T>(L0[c * PLANE + cc], B.out, vo_c, so + c * nn * W);
+      bstore<T>(nv[c], rout, vo_u, so + c * nn * W);
+      bstore<T>(L0[c * PLANE + cc], rout, vo_c, so + c * nn * W);
     }
     if constexpr (DOT) {
       // f . u_out at both nodes (f reads 0 at a node outside the box)
@@ -586,9 +597,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   constexpr int W = sizeof(T);
   const int nn = g.nn, nxy = g.nx * g.ny;
   const int vbytes = 3 * nn * W;
-  const TileBufs B{make_rsrc(u, vbytes), make_rsrc(f, MODE == 0 ? vbytes : 0),
-                   make_rsrc(psi, g.cx * g.cy * g.cz * W), make_rsrc(r, r ? vbytes : 0),
-                   make_rsrc(u, 0)};
+  const TileBufs B{u, f, psi, vbytes, g.cx * g.cy * g.cz * W};
+  const __amdgpu_buffer_rsrc_t rout = make_rsrc(r, r ? vbytes : 0);
   const int tx = lt % tg.ntx, rest = lt / tg.ntx;
   const int ty = rest % tg.nty, tz = rest / tg.nty;
   const int x0 = tx * TX, y0 = ty * TY;
@@ -603,13 +613,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
                      (gy < g.ny && gx0 + 1 < g.nx) ? (gy * g.nx + gx0 + 1) * W : kOOB};
   // f of both nodes, one plane ahead
   auto fetch_f = [&](int k, T (&fr)[2][3]) __attribute__((always_inline)) {
-    const bool ok = MODE == 0 && k < k1;
-    const __amdgpu_buffer_rsrc_t rf = ok ? B.f : B.null;
-    const int so = ok ? k * nxy * W : 0;
+    if constexpr (MODE != 0) return;
+    const __amdgpu_buffer_rsrc_t rf = make_rsrc(B.f, k < k1 ? vbytes : 0);
+    const int so = k * nxy * W;
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) fr[h][c] = bload<T>(rf, vn[h], so + (ok ? c * nn * W : 0));
+      for (int c = 0; c < 3; ++c) fr[h][c] = bload<T>(rf, vn[h], so + c * nn * W);
   };
   // MASK: the classes of both nodes of plane k, loaded a plane ahead too
   auto fetch_cls = [&](int k, int (&cl)[2]) __attribute__((always_inline)) {
@@ -635,12 +645,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) fv[h][c] = FN[h][c];
-    fetch_f(k + 1, FN);
+      for (int c = 0; c < 3; ++c) fv[h][c] = MODE == 0 ? FN[h][c] : T(0);
     const int clk[2] = {CLN[0], CLN[1]};
-    fetch_cls(k + 1, CLN);
     tile_fetch_u<T>(g, B, vu, k + 2, RU);
     tile_fetch_p<T>(g, B, vp, k + 1, RP);
+    fetch_f(k + 1, FN);
+    fetch_cls(k + 1, CLN);
     const T *Lm = su[(k + 2) % 3], *L0 = su[k % 3], *L1 = su[(k + 1) % 3];
     const T *Pm = sp[(k + 1) & 1], *P0 = sp[k & 1];
     const int so = k * nxy * W;
@@ -668,9 +678,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
           else acc += (double)L0[c * PLANE + cu] * (double)v[c];
         }
       }
-      if (r)
+      // without r the descriptor is empty and the stores are dropped (a branch
+      // around them would make every step wait for the stores of the last)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) bstore<T>(v[c], B.out, vn[h], so + c * nn * W);
+      for (int c = 0; c < 3; ++c) bstore<T>(v[c], rout, vn[h], so + c * nn * W);
     }
     __syncthreads();
     tile_put_u<T>(su[(k + 2) % 3], RU);
