@@ -86,8 +86,14 @@ template <typename T>
 hipError_t launch_residual(const Level &L, const T *psi, const Coef<T> &C, const T *u,
                            const T *f, T *r, double *partials, hipStream_t st,
                            const uint8_t *cls = nullptr, const TileList *tl = nullptr);
+// Residual-norm partials of u (as launch_residual) with the residual written
+// as r32 = fp32((f - K u) / sqrt(*ss)) (0 on displacement DOF), on a level whose
+// residual runs tiled (!residual_sweep_ok).
 hipError_t launch_residual_cast(const Level &L, const double *u, const double *f, float *r32,
-                                const double *ss, hipStream_t st);
+                                const double *ss, double *partials, hipStream_t st);
+hipError_t launch_residual_cast_tiled(const Level &L, const double *u, const double *f,
+                                      float *r32, const double *ss, double *partials,
+                                      hipStream_t st);
 template <typename T>
 hipError_t launch_jacobi(const Level &L, const T *psi, const Coef<T> &C, const T *u, const T *f,
                          T *u_out, double omega, hipStream_t st, const uint8_t *cls = nullptr);
@@ -192,8 +198,8 @@ hipError_t launch_xpby_x(const Level &L, double *x, double *p, const ZSrc &z,
                          const double *alpha, hipStream_t st);
 hipError_t launch_axpy_free(const Level &L, double *x, const double *p, const double *alpha,
                             hipStream_t st);
-// r32 = fp32(r / sqrt(*ss)) for a residual r in memory (the expression of
-// launch_residual_cast).
+// r32 = fp32(r / sqrt(*ss)) for a residual r in memory (times the reciprocal
+// of the square root).
 hipError_t launch_scale_cast(const double *r, float *r32, int64_t n, const double *ss,
                              hipStream_t st);
 // The first colour half-sweep from a zero iterate for the load f into t

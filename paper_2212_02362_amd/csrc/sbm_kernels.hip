@@ -123,35 +123,6 @@ __global__ __launch_bounds__(kBlock) void k_residual_sweep(Geom g, Coef<double> 
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-// r32 = fp32((f - K u) / s) on free DOF: the scaled residual handed to the
-// FP32 cycle of the mixed-precision solve.  s = sqrt(*ss) is the residual
-// norm the convergence test just computed (device-resident, so a captured
-// cycle needs no host-side argument).
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_residual_cast(Geom g, Coef<double> C,
-                                                          const double *__restrict__ psi,
-                                                          const double *__restrict__ u,
-                                                          const double *__restrict__ f,
-                                                          float *__restrict__ r32,
-                                                          const double *__restrict__ ss) {
-  const int64_t id = (int64_t)xcd_block() * kBlock + threadIdx.x;
-  if (id >= g.nn) return;
-  const double sn = sqrt(*ss);
-  const double inv_s = sn > 0.0 ? 1.0 / sn : 0.0;
-  int i, j, k;
-  node_ijk(g, id, i, j, k);
-  double fv[3], out[3], dg[3];
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) fv[c] = f[c * g.nn + id];
-  node_stencil<double, DIM>(g, C, psi, u, i, j, k, out, dg);
-  const uint32_t fb = face_bits(g, i, j, k);
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) {
-    const float v = (float)((fv[c] - out[c]) * inv_s);
-    r32[c * g.nn + id] = ((g.dmask >> c) & fb) ? 0.0f : v;
-  }
-}
-
 // ------------------------------------------------------------- smoothers --
 
 // Damped Jacobi (Sec. 2.3): u_out = u + omega D^-1 (f - K u) on free DOF.
@@ -941,8 +912,8 @@ __global__ __launch_bounds__(kBlock) void k_cast_scaled(const double *__restrict
   r32[q] = sn > 0.0 ? (float)(r[q] / sn) : 0.0f;
 }
 
-// r32 = fp32(r / s) as k_residual_cast forms it (times the reciprocal of
-// s = sqrt(*ss)), for a residual r already in memory.
+// r32 = fp32(r / s) (times the reciprocal of s = sqrt(*ss)) for a residual r
+// in memory.
 __global__ __launch_bounds__(kBlock) void k_scale_cast(const double *__restrict__ r,
                                                        float *__restrict__ r32, int64_t n,
                                                        const double *__restrict__ ss) {
@@ -1343,12 +1314,9 @@ hipError_t launch_residual_sweep(const Level &L, const double *u, const double *
 bool residual_sweep_ok(const Level &L) { return !use_tiled(L); }
 
 hipError_t launch_residual_cast(const Level &L, const double *u, const double *f, float *r32,
-                                const double *ss, hipStream_t st) {
-  if (L.g.dim == 3)
-    SBM_LAUNCH((k_residual_cast<3>), grid_blocks(L.g.nn), kBlock, st, L.g, L.c64, L.psi64, u, f,
-               r32, ss);
-  SBM_LAUNCH((k_residual_cast<2>), grid_blocks(L.g.nn), kBlock, st, L.g, L.c64, L.psi64, u, f, r32,
-             ss);
+                                const double *ss, double *partials, hipStream_t st) {
+  if (!use_tiled(L)) return hipErrorInvalidValue;
+  return launch_residual_cast_tiled(L, u, f, r32, ss, partials, st);
 }
 
 template <typename T>

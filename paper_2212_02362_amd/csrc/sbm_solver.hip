@@ -94,7 +94,8 @@ struct sbm_ctx {
     int mode;  // 0: outer-loop cycle on x0, 1: preconditioner z = M r, 2: as 0 with work
                // done by the convergence test (FP64: the first finest half-sweep;
                // mixed: the finest residual), 3: mixed, also the FP32 cycle's first
-               // half-sweep made by the cast
+               // half-sweep made by the cast, 4: mixed preconditioner on a load the CG
+               // update cast, 5: mixed, the convergence test cast the residual
     int precision;
     const double *f;
     bool prof;
@@ -602,10 +603,29 @@ static sbm_status residual_norm2_keep(sbm_ctx *c, const double *u, const double 
   return SBM_OK;
 }
 
+// As residual_norm2 on a tiled finest level, the residual written as the FP32
+// cycle's load fp32((f - K u) / s), s^2 = scal[8]: the norm of the residual
+// before (the lifted load's at first).  The cycle is linear in its load, so any
+// positive scale near its size does; this one is known before the pass.
+static sbm_status residual_norm2_cast(sbm_ctx *c, const double *u, const double *f,
+                                      double *out) {
+  Level &L = c->L[0];
+  {
+    ProfScope ps(c, SBM_PROF_NORM, true);
+    HIP_TRY(launch_residual_cast(L, u, f, L.f32, c->scal + 8, c->partials, c->st));
+  }
+  HIP_TRY(launch_finalize_sum(c->partials, stencil_partials(L), c->scal, c->st));
+  HIP_TRY(hipMemcpyAsync(c->host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->st));
+  HIP_TRY(hipStreamSynchronize(c->st));
+  if (c->prof_on) prof_harvest(c);
+  *out = c->host[0];
+  return SBM_OK;
+}
+
 // One cycle of the outer loop on the finest iterate x0 for the load f: an
 // FP64 V-cycle, or (mixed) r32 = (f - K x0)/s, an FP32 V-cycle for e32 from
 // zero, x0 += s e32 with s the residual norm left in scal[0] by the
-// convergence test.
+// convergence test (mode 5: s^2 = scal[8], then scal[0] becomes the next one).
 static hipError_t cycle_body(sbm_ctx *c, const double *f, int mode) {
   Level &L0 = c->L[0];
   const int64_t nv = (int64_t)c->dim * L0.g.nn;
@@ -681,10 +701,12 @@ static hipError_t cycle_body(sbm_ctx *c, const double *f, int mode) {
       if (e != hipSuccess) return e;
       return launch_correct(L0, c->x0, L0.e32, c->scal, c->st);
     }
-    // mode 2: the convergence test left f - K x0 in the finest tmp vector
-    if ((e = mode == 2 ? launch_scale_cast(L0.t, L0.f32, nv, c->scal, c->st)
-                       : launch_residual_cast(L0, c->x0, f, L0.f32, c->scal, c->st)) != hipSuccess)
+    // mode 2: the convergence test left f - K x0 in the finest tmp vector;
+    // mode 5: it left the FP32 load itself
+    if (mode == 2 &&
+        (e = launch_scale_cast(L0.t, L0.f32, nv, c->scal, c->st)) != hipSuccess)
       return e;
+    const double *ss = mode == 5 ? c->scal + 8 : c->scal;
     if (tiled_ok(L0) && c->opt.smoother == 0 && c->opt.nu_pre >= 1 && c->nlev > 1 &&
         c->tail32 != 0)
       c->zero_start = true;
@@ -693,7 +715,8 @@ static hipError_t cycle_body(sbm_ctx *c, const double *f, int mode) {
     e = vcycle<float>(c, 0, L0.e32, L0.f32, L0.t32);
     c->zero_start = false;
     if (e != hipSuccess) return e;
-    return launch_correct(L0, c->x0, L0.e32, c->scal, c->st);
+    if ((e = launch_correct(L0, c->x0, L0.e32, ss, c->st)) != hipSuccess) return e;
+    return mode == 5 ? launch_copy<double>(c->scal, c->scal + 8, 1, c->st) : hipSuccess;
   }
   c->first_half_done = mode == 2;
   e = vcycle<double>(c, 0, c->x0, f, L0.t);
@@ -924,12 +947,16 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
   // also makes the FP32 cycle's first half-sweep when the finest level
   // smooths outside the tail
   const bool keep = c->opt.precision == 1 && residual_sweep_ok(L0);
+  // mixed on a tiled finest level: the convergence test casts
+  const bool cast = c->opt.precision == 1 && !keep;
+  if (cast) HIP_TRY(launch_fill<double>(c->scal + 8, 1, fnorm * fnorm, c->st));
   const bool keep_sweep = keep && c->opt.smoother == 0 && c->opt.nu_pre >= 1 && c->nlev > 1 &&
                           c->tail32 != 0;
   for (m = 0;; ++m) {
     double ss = 0.0;
     sbm_status s = fused  ? residual_norm2_sweep(c, c->x0, f, &ss)
                    : keep ? residual_norm2_keep(c, c->x0, f, &ss)
+                   : cast ? residual_norm2_cast(c, c->x0, f, &ss)
                           : residual_norm2(c, c->x0, f, &ss);
     if (s != SBM_OK) return s;
     rho = fnorm > 0.0 ? sqrt(ss) / fnorm : (ss > 0.0 ? INFINITY : 0.0);
@@ -953,7 +980,7 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
       status = SBM_NOT_CONVERGED;
       break;
     }
-    s = run_cycle(c, f, keep_sweep ? 3 : (fused || keep ? 2 : 0));
+    s = run_cycle(c, f, keep_sweep ? 3 : cast ? 5 : (fused || keep ? 2 : 0));
     if (s != SBM_OK) return s;
   }
   if (ncyc) *ncyc = m;

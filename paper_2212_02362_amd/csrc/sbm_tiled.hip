@@ -537,14 +537,25 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   }
 }
 
+// Where a residual pass writes fp32(r / s), s = sqrt(*ss) (MODE 2 below).
+struct CastOut {
+  float *r32;
+  const double *ss;
+};
+__device__ __forceinline__ double inv_sqrt(double ss) {
+  const double s = sqrt(ss);
+  return s > 0.0 ? 1.0 / s : 0.0;
+}
+
 // A face block of a whole-level k_full_tile pass: one node per thread, the
 // block's sum in partials[ntiles + fb].
 template <typename T, typename CO, int MODE, bool MASK>
 __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const T *psi, const T *u,
                                                 const T *f, T *r, double *partials,
                                                 const TileGeom &tg, const uint8_t *cls, int fb,
-                                                double *red) {
+                                                double *red, const CastOut &co) {
   const int nn = g.nn;
+  const double inv_s = MODE == 2 ? inv_sqrt(*co.ss) : 0.0;
   double acc = 0.0;
   int x, y, z;
   if (face_node(g, tg, fb * NT + (int)threadIdx.x, x, y, z)) {
@@ -555,15 +566,17 @@ __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const 
       node_stencil<T, 3, true, TG, CO>(g, C, psi, u, x, y, z, out, dg, uc);
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const T val = MODE == 0 ? f[c * nn + q] - out[c] : out[c];
+        const T val = MODE != 1 ? f[c * nn + q] - out[c] : out[c];
         v[c] = tg_dirichlet(g, x, y, z, c) ? T(0) : val;
-        if (MODE == 0) acc += (double)v[c] * (double)v[c];
+        if (MODE != 1) acc += (double)v[c] * (double)v[c];
         else acc += (double)uc[c] * (double)v[c];
       }
     }
-    if (r)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) r[c * nn + q] = v[c];
+    for (int c = 0; c < 3; ++c) {
+      if (MODE == 2) co.r32[c * nn + q] = (float)(v[c] * inv_s);
+      else if (r) r[c * nn + q] = v[c];
+    }
   }
   if (partials) {
     const double sum = block_sum(acc, red);
@@ -576,20 +589,24 @@ __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const 
 //     with MASK, outside classes 1-3); r = v when r is given; partial sum of
 //     v^2 per tile when partials is given;
 //   MODE 1 (Krylov Apply): v = K u on free DOF, 0 on displacement DOF; r = v;
-//     partial sum of u . v per tile.
+//     partial sum of u . v per tile;
+//   MODE 2 (FP64, the mixed cycle's convergence test): as MODE 0 with partials,
+//     and the residual leaves as the FP32 cycle's load fp32(v / s) (CastOut)
+//     instead of r: 68 B per node, where the test and a second, node-parallel
+//     residual pass for the cast took 56 + 68 B and 831 us at 257^3 (339 us).
 // Partials land in partials[tile], tiles in their logical order, then one per
 // face block (partials[ntiles + face block]).
 template <typename T, typename CO, int MODE, bool MASK>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_full_tile(
     TG g, CO C, const T *__restrict__ psi, const T *__restrict__ u, const T *__restrict__ f,
     T *__restrict__ r, double *__restrict__ partials, TileGeom tg,
-    const uint8_t *__restrict__ cls, const int *__restrict__ ids, int n) {
+    const uint8_t *__restrict__ cls, const int *__restrict__ ids, int n, CastOut co) {
   __shared__ T su[3][SLOT_U];
   __shared__ T sp[2][SLOT_P];
   __shared__ double red[NT / 64 + 1];
   const int li = tile_or_face(n);
   if (li < 0) {
-    full_face_block<T, CO, MODE, MASK>(g, C, psi, u, f, r, partials, tg, cls, -1 - li, red);
+    full_face_block<T, CO, MODE, MASK>(g, C, psi, u, f, r, partials, tg, cls, -1 - li, red, co);
     return;
   }
   if (li >= n) return;
@@ -598,7 +615,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   const int nn = g.nn, nxy = g.nx * g.ny;
   const int vbytes = 3 * nn * W;
   const TileBufs B{u, f, psi, vbytes, g.cx * g.cy * g.cz * W};
-  const __amdgpu_buffer_rsrc_t rout = make_rsrc(r, r ? vbytes : 0);
+  const __amdgpu_buffer_rsrc_t rout = MODE == 2 ? make_rsrc(co.r32, vbytes / 2)
+                                                : make_rsrc(r, r ? vbytes : 0);
+  const double inv_s = MODE == 2 ? inv_sqrt(*co.ss) : 0.0;
   const int tx = lt % tg.ntx, rest = lt / tg.ntx;
   const int ty = rest % tg.nty, tz = rest / tg.nty;
   const int x0 = tx * TX, y0 = ty * TY;
@@ -613,7 +632,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
                      (gy < g.ny && gx0 + 1 < g.nx) ? (gy * g.nx + gx0 + 1) * W : kOOB};
   // f of both nodes, one plane ahead
   auto fetch_f = [&](int k, T (&fr)[2][3]) __attribute__((always_inline)) {
-    if constexpr (MODE != 0) return;
+    if constexpr (MODE == 1) return;
     const __amdgpu_buffer_rsrc_t rf = make_rsrc(B.f, k < k1 ? vbytes : 0);
     const int so = k * nxy * W;
 #pragma unroll
@@ -645,7 +664,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) fv[h][c] = MODE == 0 ? FN[h][c] : T(0);
+      for (int c = 0; c < 3; ++c) fv[h][c] = MODE != 1 ? FN[h][c] : T(0);
     const int clk[2] = {CLN[0], CLN[1]};
     tile_fetch_u<T>(g, B, vu, k + 2, RU);
     tile_fetch_p<T>(g, B, vp, k + 1, RP);
@@ -672,16 +691,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           const bool fixed = face && tg_dirichlet(g, gx, gy, k, c);
-          const T val = MODE == 0 ? fv[h][c] - out[c] : out[c];
+          const T val = MODE != 1 ? fv[h][c] - out[c] : out[c];
           v[c] = fixed ? T(0) : val;
-          if (MODE == 0) acc += (double)v[c] * (double)v[c];
+          if (MODE != 1) acc += (double)v[c] * (double)v[c];
           else acc += (double)L0[c * PLANE + cu] * (double)v[c];
         }
       }
       // without r the descriptor is empty and the stores are dropped (a branch
       // around them would make every step wait for the stores of the last)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) bstore<T>(v[c], rout, vn[h], so + c * nn * W);
+      for (int c = 0; c < 3; ++c) {
+        if constexpr (MODE == 2)  // FP32: half the byte offsets (kOOB / 2 is past the end too)
+          bstore<float>((float)(v[c] * inv_s), rout, vn[h] >> 1, (so + c * nn * W) >> 1);
+        else
+          bstore<T>(v[c], rout, vn[h], so + c * nn * W);
+      }
     }
     __syncthreads();
     tile_put_u<T>(su[(k + 2) % 3], RU);
@@ -1588,7 +1612,7 @@ int tiled_partials(const Level &L) {
 template <typename T, int MODE>
 static void full_tiled(const Level &L, const T *psi, const Coef<T> &C, const T *u, const T *f,
                        T *r, double *partials, hipStream_t st, const uint8_t *cls,
-                       const TileList *tl) {
+                       const TileList *tl, const CastOut &co = CastOut{}) {
   const TG gg = make_tg(L.g);
   const TileGeom tg =
       tile_geom(gg, tl == nullptr, tl ? tl->kz : 0, tile_target<T>(TileKind::full));
@@ -1599,18 +1623,16 @@ static void full_tiled(const Level &L, const T *psi, const Coef<T> &C, const T *
   const int nface = tl ? 0 : tg.nface;
   if (n + nface > 0) {
     const dim3 grid(tiled_grid(n, nface)), block(NT);
-    if (cls && cubic)
-      hipLaunchKernelGGL((k_full_tile<T, CoefCubic<T>, MODE, true>), grid, block, 0, st, gg, cc,
-                         psi, u, f, r, partials, tg, cls, ids, n);
-    else if (cls)
-      hipLaunchKernelGGL((k_full_tile<T, Coef<T>, MODE, true>), grid, block, 0, st, gg, C, psi,
-                         u, f, r, partials, tg, cls, ids, n);
-    else if (cubic)
-      hipLaunchKernelGGL((k_full_tile<T, CoefCubic<T>, MODE, false>), grid, block, 0, st, gg, cc,
-                         psi, u, f, r, partials, tg, cls, ids, n);
-    else
-      hipLaunchKernelGGL((k_full_tile<T, Coef<T>, MODE, false>), grid, block, 0, st, gg, C, psi,
-                         u, f, r, partials, tg, cls, ids, n);
+    auto go = [&](auto &&cf, auto mask) {
+      hipLaunchKernelGGL((k_full_tile<T, std::decay_t<decltype(cf)>, MODE, decltype(mask)::value>),
+                         grid, block, 0, st, gg, cf, psi, u, f, r, partials, tg, cls, ids, n, co);
+    };
+    if constexpr (MODE != 2) {
+      if (cls && cubic) return go(cc, std::true_type{});
+      if (cls) return go(C, std::true_type{});
+    }
+    if (cubic) go(cc, std::false_type{});
+    else go(C, std::false_type{});
   }
 }
 
@@ -1629,6 +1651,15 @@ hipError_t launch_apply_dot_tiled(const Level &L, const double *p, double *q, do
   (void)hipGetLastError();
   full_tiled<double, 1>(L, L.psi64, L.c64, p, (const double *)nullptr, q, partials, st, nullptr,
                         nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_residual_cast_tiled(const Level &L, const double *u, const double *f,
+                                      float *r32, const double *ss, double *partials,
+                                      hipStream_t st) {
+  (void)hipGetLastError();
+  full_tiled<double, 2>(L, L.psi64, L.c64, u, f, (double *)nullptr, partials, st, nullptr,
+                        nullptr, CastOut{r32, ss});
   return hipGetLastError();
 }
 
