@@ -26,7 +26,7 @@ struct DispValues {
 };
 
 struct Level {
-  Geom g;
+  GeomS g;
   double h[3];
   Coef<double> c64;
   Coef<float> c32;
@@ -35,6 +35,8 @@ struct Level {
   // FP64 vectors: level 0 uses f (load), r (residual / ping-pong); coarse
   // levels use e (correction), f (restricted residual), t (ping-pong / residual)
   double *e = nullptr, *f = nullptr, *t = nullptr;
+  double *fs = nullptr;  // finest level: the load in split rows
+  int hx64 = 0, hx32 = 0;  // g.hx while a solve with FP64 / FP32 cycles runs
   // FP32 vectors of the mixed cycle
   float *e32 = nullptr, *f32 = nullptr, *t32 = nullptr;
 };
@@ -114,14 +116,17 @@ bool residual_sweep_ok(const Level &L);
 hipError_t launch_residual_sweep(const Level &L, const double *u, const double *f,
                                  double *u_out, double omega, int colour, double *partials,
                                  hipStream_t st);
-// LDS-tiled 3D half-sweep (same result as launch_rb_half); tiled_ok tells
-// whether a level is large enough for the 64 x 8 node tiles to pay.  With a
-// tile list only those tiles are swept (nodes outside them stay untouched).
-// With partials (whole level, no classes) the launch also writes the partial
-// sums of f . u_out over free DOF, rb_tiled_partials(L, fp32) of them; an
-// FP32 launch then reads the FP64 residual r64 instead of f (its load is
-// fp32(r64 / s), s = sqrt(*ss), as the mixed cast makes it) and sums
-// r64 . (s u_out).
+// On a level with split rows only the relaxed colour is written.
+hipError_t launch_residual_sweep_tiled(const Level &L, const double *u, const double *f,
+                                       double *half, double omega, int colour, double *partials,
+                                       hipStream_t st);
+// LDS-tiled 3D half-sweep on natural rows (same result as launch_rb_half);
+// tiled_ok tells whether a level is large enough for the 64 x 8 node tiles to
+// pay.  With a tile list only those tiles are swept (nodes outside them stay
+// untouched).  With partials (FP32, whole level, no classes) the launch also
+// writes the partial sums of r64 . (s u_out) over free DOF, rb_tiled_partials(L)
+// of them, and takes its load from the FP64 residual r64: fp32(r64 / s), s =
+// sqrt(*ss), as the mixed cast makes it.
 bool tiled_ok(const Level &L);
 // Levels whose colour half-sweeps take the tiled kernel (a superset of
 // tiled_ok: the half-sweep pays from smaller levels than the other passes).
@@ -132,7 +137,30 @@ hipError_t launch_rb_tiled(const Level &L, const T *psi, const Coef<T> &C, const
                            const uint8_t *cls = nullptr, const TileList *tl = nullptr,
                            double *partials = nullptr, const double *r64 = nullptr,
                            const double *ss = nullptr);
-int rb_tiled_partials(const Level &L, bool fp32);
+int rb_tiled_partials(const Level &L);
+// Whether a solve with FP64 / FP32 cycles keeps a level's vectors in split rows
+// (its bottom level excepted).
+bool split_level(const Level &L, bool fp32);
+// Colour half-sweep on split rows: the nodes of `colour` relaxed from us (the
+// buffer holding that colour; nullptr: it is zero) and uo (the other colour's)
+// into u_out, which must not be us; nothing else is written.  With partials
+// (FP64) also the partial sums of f . u_out over free DOF of both colours (the
+// other one's u from uo), rb_split_partials(L) of them.
+template <typename T>
+hipError_t launch_rb_split(const Level &L, const T *psi, const Coef<T> &C, const T *us,
+                           const T *uo, const T *f, T *u_out, double omega, int colour,
+                           hipStream_t st, double *partials = nullptr);
+int rb_split_partials(const Level &L);
+// Node vectors between natural rows and the level's (a copy where it has
+// natural rows).
+template <typename T>
+hipError_t launch_to_split(const Level &L, const T *src, T *dst, hipStream_t st);
+template <typename T>
+hipError_t launch_from_split(const Level &L, const T *src, T *dst, hipStream_t st);
+// A load given in natural rows, 0 on displacement DOF, in the level's rows, and
+// num_blocks(nn) partial sums of its squares.
+hipError_t launch_take_load(const Level &L, const double *f, double *out, double *partials,
+                            hipStream_t st);
 // Levels whose first sweep from a zero iterate runs as one launch
 // (launch_rb_fused with u == nullptr).
 bool zero_sweep_ok(const Level &L);
@@ -202,10 +230,11 @@ hipError_t launch_axpy_free(const Level &L, double *x, const double *p, const do
 // of the square root).
 hipError_t launch_scale_cast(const double *r, float *r32, int64_t n, const double *ss,
                              hipStream_t st);
-// The first colour half-sweep from a zero iterate for the load f into t
-// (finest level, FP64 operator).
-hipError_t launch_zero_sweep(const Level &L, const double *f, double *t, double omega, int colour,
-                             hipStream_t st);
+// The first colour half-sweep from a zero iterate for the load f into t (split
+// rows: the relaxed colour alone, else zeros at the other nodes).
+template <typename T>
+hipError_t launch_zero_sweep(const Level &L, const T *psi, const Coef<T> &C, const T *f, T *t,
+                             double omega, int colour, hipStream_t st);
 // ... and the first colour half-sweep of the FP32 correction from zero into
 // t32 (finest level, FP32 operator).
 hipError_t launch_scale_cast_sweep(const Level &L, const double *r, float *r32, float *t32,

@@ -51,8 +51,8 @@ __global__ __launch_bounds__(kBlock) void k_apply(Geom g, Coef<T> C, const T *__
 // MASK: a class array is given and only classes 1-3 (interior, interface,
 // first outer layer: the padded region of an adaptive level) carry a
 // residual; elsewhere r = 0.
-template <typename T, int DIM, bool MASK>
-__global__ __launch_bounds__(kBlock) void k_residual(Geom g, Coef<T> C, const T *__restrict__ psi,
+template <typename T, int DIM, bool MASK, typename G>
+__global__ __launch_bounds__(kBlock) void k_residual(G g, Coef<T> C, const T *__restrict__ psi,
                                                      const T *__restrict__ u,
                                                      const T *__restrict__ f, T *__restrict__ r,
                                                      double *__restrict__ partials,
@@ -128,8 +128,8 @@ __global__ __launch_bounds__(kBlock) void k_residual_sweep(Geom g, Coef<double> 
 // Damped Jacobi (Sec. 2.3): u_out = u + omega D^-1 (f - K u) on free DOF.
 // MASK: a class array is given and only class-1 nodes (the unknowns of an
 // adaptive level) are relaxed; every other node is copied.
-template <typename T, int DIM, bool MASK>
-__global__ __launch_bounds__(kBlock) void k_jacobi(Geom g, Coef<T> C, const T *__restrict__ psi,
+template <typename T, int DIM, bool MASK, typename G>
+__global__ __launch_bounds__(kBlock) void k_jacobi(G g, Coef<T> C, const T *__restrict__ psi,
                                                    const T *__restrict__ u,
                                                    const T *__restrict__ f,
                                                    T *__restrict__ u_out, T omega,
@@ -221,8 +221,8 @@ __global__ __launch_bounds__(kBlock) void k_rb_half(Geom g, Coef<T> C, const T *
 // f_coarse(I) = 2^-d sum_n P(n, I) r(n): full weighting [1/2, 1, 1/2] per axis
 // around the coincident fine node 2I; fine nodes outside the box are absent.
 // The coarse node (I, J, K) with linear index id.
-template <typename T, int DIM>
-__device__ __forceinline__ void restrict_node(const Geom &gf, const Geom &gc, const T *r, T *fc,
+template <typename T, int DIM, typename G>
+__device__ __forceinline__ void restrict_node(const G &gf, const G &gc, const T *r, T *fc,
                                               T *ec, int64_t id, int I, int J, int K) {
   // Branch-free gather (all 27 loads in flight together): a neighbour outside
   // the box is read at the centre with weight 0, which adds an exact zero, so
@@ -246,7 +246,8 @@ __device__ __forceinline__ void restrict_node(const Geom &gf, const Geom &gc, co
         const int fi = 2 * I + dx;
         const bool okx = fi >= 0 && fi < gf.nx;
         const T w = wz * wy * (okx ? (dx == 0 ? T(1) : T(0.5)) : T(0));
-        const int64_t q = (okx ? fi : 2 * I) + (int64_t)gf.nx * (fjc + (int64_t)gf.ny * fkc);
+        const int64_t q = split_x(rows_hx(gf), okx ? fi : 2 * I) +
+                          (int64_t)gf.nx * (fjc + (int64_t)gf.ny * fkc);
 #pragma unroll
         for (int c = 0; c < DIM; ++c) acc[c] += w * r[c * gf.nn + q];
       }
@@ -260,13 +261,14 @@ __device__ __forceinline__ void restrict_node(const Geom &gf, const Geom &gc, co
   }
 }
 
-template <typename T, int DIM>
-__global__ __launch_bounds__(kBlock) void k_restrict(Geom gf, Geom gc, const T *__restrict__ r,
+template <typename T, int DIM, typename G>
+__global__ __launch_bounds__(kBlock) void k_restrict(G gf, G gc, const T *__restrict__ r,
                                                      T *__restrict__ fc, T *__restrict__ ec) {
-  const int64_t id = (int64_t)xcd_block() * (int)blockDim.x + threadIdx.x;
-  if (id >= gc.nn) return;
+  const int64_t t = (int64_t)xcd_block() * (int)blockDim.x + threadIdx.x;
+  if (t >= gc.nn) return;
   int I, J, K;
-  node_ijk(gc, id, I, J, K);
+  node_ijk_natural(gc, t, I, J, K);
+  const int64_t id = t - I + split_x(rows_hx(gc), I);
   restrict_node<T, DIM>(gf, gc, r, fc, ec, id, I, J, K);
 }
 
@@ -309,7 +311,7 @@ static RTile restrict_tiles(const Geom &gc) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(RNT) void k_restrict_tile(Geom gf, Geom gc, RTile rt,
+__global__ __launch_bounds__(RNT) void k_restrict_tile(GeomS gf, GeomS gc, RTile rt,
                                                        const T *__restrict__ r,
                                                        T *__restrict__ fc, T *__restrict__ ec) {
   __shared__ T sw[2][RPT * RNT];  // padded: every thread stores all its slots
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(RNT) void k_restrict_tile(Geom gf, Geom gc, RTile r
       const int lx = s < RHE ? 2 * s : 2 * (s - RHE) + 1;
       const int gx = 2 * I0 - 1 + lx, gy = 2 * J0 - 1 + y;
       if (lx <= 2 * RCX && gx >= 0 && gx < gf.nx && gy >= 0 && gy < gf.ny)
-        off[j] = (int)(c * gf.nn + gx + (int64_t)gf.nx * gy);
+        off[j] = (int)(c * gf.nn + split_x(rows_hx(gf), gx) + (int64_t)gf.nx * gy);
     }
   }
   auto fetch = [&](int fz, T (&v)[RPT]) __attribute__((always_inline)) {
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(RNT) void k_restrict_tile(Geom gf, Geom gc, RTile r
 #pragma unroll
         for (int q = 0; q < 9; ++q) acc[c] += pv[c][q];
       if (own) {
-        const int64_t id = I + (int64_t)gc.nx * (J + (int64_t)gc.ny * K);
+        const int64_t id = split_x(rows_hx(gc), I) + (int64_t)gc.nx * (J + (int64_t)gc.ny * K);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           fc[c * gc.nn + id] = is_dirichlet(gc, I, J, K, c) ? T(0) : acc[c] * T(0.125);
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(RNT) void k_restrict_tile(Geom gf, Geom gc, RTile r
 // The coarse nodes the tiles leave (column cxn and row cyn of a 2^n + 1
 // coarse level), node-parallel as k_restrict.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_restrict_rest(Geom gf, Geom gc, RTile rt,
+__global__ __launch_bounds__(kBlock) void k_restrict_rest(GeomS gf, GeomS gc, RTile rt,
                                                           const T *__restrict__ r,
                                                           T *__restrict__ fc, T *__restrict__ ec,
                                                           int n) {
@@ -436,7 +438,7 @@ __global__ __launch_bounds__(kBlock) void k_restrict_rest(Geom gf, Geom gc, RTil
     I = q - ncol * gc.ny;
     J = rt.cyn;
   }
-  const int64_t id = I + (int64_t)gc.nx * (J + (int64_t)gc.ny * K);
+  const int64_t id = split_x(rows_hx(gc), I) + (int64_t)gc.nx * (J + (int64_t)gc.ny * K);
   restrict_node<T, 3>(gf, gc, r, fc, ec, id, I, J, K);
 }
 
@@ -447,14 +449,14 @@ __global__ __launch_bounds__(kBlock) void k_restrict_rest(Geom gf, Geom gc, RTil
 // Loads are clamped at the last coarse / fine node; a fine node that does not
 // exist (2I + 1 past the end) is the clamped one and receives that node's own
 // value, so every store is unconditional and every load is in flight at once.
-template <typename T, int DIM>
-__global__ __launch_bounds__(kBlock) void k_prolong_add(Geom gf, Geom gc, const T *__restrict__ e,
+template <typename T, int DIM, typename G>
+__global__ __launch_bounds__(kBlock) void k_prolong_add(G gf, G gc, const T *__restrict__ e,
                                                         T *__restrict__ u) {
   constexpr int NZ = (DIM == 3) ? 2 : 1;
   const int64_t id = (int64_t)xcd_block() * (int)blockDim.x + threadIdx.x;
   if (id >= gc.nn) return;
   int I, J, K;
-  node_ijk(gc, id, I, J, K);
+  node_ijk_natural(gc, id, I, J, K);
   const int I1 = min(I + 1, gc.nx - 1), J1 = min(J + 1, gc.ny - 1);
   const int K1 = (DIM == 3) ? min(K + 1, gc.nz - 1) : K;
   T ev[NZ][2][2][3], uv[NZ][2][2][3];
@@ -467,10 +469,11 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(Geom gf, Geom gc, const 
     for (int a = 0; a < 2; ++a)
 #pragma unroll
       for (int o = 0; o < 2; ++o) {
-        const int64_t q = (o ? I1 : I) + (int64_t)gc.nx * ((a ? J1 : J) + (int64_t)gc.ny * (b ? K1 : K));
+        const int64_t q = split_x(rows_hx(gc), o ? I1 : I) +
+                          (int64_t)gc.nx * ((a ? J1 : J) + (int64_t)gc.ny * (b ? K1 : K));
         const int fi = 2 * I + (o && ex ? 1 : 0), fj = 2 * J + (a && ey ? 1 : 0);
         const int fk = (DIM == 3) ? 2 * K + (b && ez ? 1 : 0) : 0;
-        fq[b][a][o] = fi + (int64_t)gf.nx * (fj + (int64_t)gf.ny * fk);
+        fq[b][a][o] = split_x(rows_hx(gf), fi) + (int64_t)gf.nx * (fj + (int64_t)gf.ny * fk);
 #pragma unroll
         for (int c = 0; c < DIM; ++c) {
           ev[b][a][o][c] = e[c * gc.nn + q];
@@ -533,8 +536,8 @@ __global__ __launch_bounds__(kBlock) void k_convert(const S *__restrict__ s, D *
 }
 
 // u += s * e32 on free DOF (FP64 correction of the mixed cycle), s = sqrt(*ss).
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_correct(Geom g, double *__restrict__ u,
+template <int DIM, typename G>
+__global__ __launch_bounds__(kBlock) void k_correct(G g, double *__restrict__ u,
                                                     const float *__restrict__ e32,
                                                     const double *__restrict__ ss) {
   const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -662,6 +665,47 @@ __global__ __launch_bounds__(kBlock) void k_rhs(Geom g, Traction tr, const doubl
   }
 }
 
+// A load given in natural rows, masked (0 on displacement DOF) and written in
+// the rows of split pitch hs (0: natural); partial sums of its squares.
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_take_load(Geom g, int hs, const double *__restrict__ f,
+                                                      double *__restrict__ out,
+                                                      double *__restrict__ partials) {
+  __shared__ double lds[kBlock / 64 + 1];
+  const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  double ss = 0.0;
+  if (id < g.nn) {
+    int i, j, k;
+    node_ijk_natural(g, id, i, j, k);
+    const int64_t ds = split_x(hs, i) - i;
+    const uint32_t fb = face_bits(g, i, j, k);
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+      const double v = ((g.dmask >> c) & fb) ? 0.0 : f[c * g.nn + id];
+      out[c * g.nn + id + ds] = v;
+      ss += v * v;
+    }
+  }
+  const double s = block_sum(ss, lds);
+  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+}
+
+// A node vector between natural and split rows (to_split: from natural).
+template <typename T, bool TO_SPLIT>
+__global__ __launch_bounds__(kBlock) void k_relayout(Geom g, int comps, int hs,
+                                                     const T *__restrict__ src,
+                                                     T *__restrict__ dst) {
+  const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (id >= g.nn) return;
+  int i, j, k;
+  node_ijk_natural(g, id, i, j, k);
+  const int64_t q = id + split_x(hs, i) - i;
+  for (int c = 0; c < comps; ++c) {
+    if (TO_SPLIT) dst[c * g.nn + q] = src[c * g.nn + id];
+    else dst[c * g.nn + id] = src[c * g.nn + q];
+  }
+}
+
 // Flags a free DOF whose diagonal vanishes (no solid cell around it).
 template <int DIM>
 __global__ __launch_bounds__(kBlock) void k_check_diag(Geom g, const double *__restrict__ psi,
@@ -736,8 +780,8 @@ __device__ __forceinline__ double zload(const ZSrc &zs, double sc, int64_t q) {
   return zs.z ? zs.z[q] : sc * (double)zs.e[q];
 }
 
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_dot_free(Geom g, const double *__restrict__ a,
+template <int DIM, typename G>
+__global__ __launch_bounds__(kBlock) void k_dot_free(G g, const double *__restrict__ a,
                                                      ZSrc b, double *__restrict__ partials) {
   __shared__ double lds[kBlock / 64 + 1];
   const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -800,8 +844,8 @@ __global__ __launch_bounds__(kBlock) void k_apply_dot(Geom g, Coef<double> C,
 // k_axpy_free: the same products, one vector pass fewer.  With r32 the new
 // residual is also cast for the mixed preconditioner: r32 = fp32(r / s) with
 // s = sqrt(*ss) (0 on displacement DOF), as k_cast_scaled forms it.
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_cg_update_r(Geom g, double *__restrict__ r,
+template <int DIM, typename G>
+__global__ __launch_bounds__(kBlock) void k_cg_update_r(G g, double *__restrict__ r,
                                                         const double *__restrict__ q, ZSrc z,
                                                         const double *__restrict__ rz,
                                                         const double *__restrict__ pq,
@@ -854,8 +898,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_update_r(Geom g, double *__restri
 // The deferred iterate update and the new direction in one pass: on free DOF
 // x += (*alpha) p (when alpha is given), then p = z + beta p, beta = (rznew -
 // rzold) / rz (beta = 0 when rz is NULL: restart); p = 0 on displacement DOF.
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_xpby_x(Geom g, double *__restrict__ x,
+template <int DIM, typename G>
+__global__ __launch_bounds__(kBlock) void k_xpby_x(G g, double *__restrict__ x,
                                                    double *__restrict__ p, ZSrc z,
                                                    const double *__restrict__ rznew,
                                                    const double *__restrict__ rzold,
@@ -885,8 +929,8 @@ __global__ __launch_bounds__(kBlock) void k_xpby_x(Geom g, double *__restrict__ 
 }
 
 // x += (*alpha) p on free DOF (the deferred CG update, when the iteration ends).
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_axpy_free(Geom g, double *__restrict__ x,
+template <int DIM, typename G>
+__global__ __launch_bounds__(kBlock) void k_axpy_free(G g, double *__restrict__ x,
                                                       const double *__restrict__ p,
                                                       const double *__restrict__ alpha) {
   const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -1265,12 +1309,24 @@ __global__ __launch_bounds__(kBlock) void k_sensitivity(Geom g, double lame, dou
 // The tiled stencil kernels write one partial sum per tile; they are used
 // where they pay and where their partials fit the per-node-block count.
 static bool use_tiled(const Level &L) {
-  return tiled_ok(L) && tiled_partials(L) <= num_blocks(L.g.nn);
+  return (L.g.hx != 0 || tiled_ok(L)) && tiled_partials(L) <= num_blocks(L.g.nn);
 }
 
 int stencil_partials(const Level &L) {
   return use_tiled(L) ? tiled_partials(L) : grid_blocks(L.g.nn);
 }
+
+// Launches with the geometry of a level's rows: kernels on natural rows carry no
+// trace of the split ones (a run-time choice cost the small levels 1 %).
+template <typename F>
+static hipError_t by_rows(const GeomS &g, F &&launch) {
+  return g.hx ? launch(g) : launch((const Geom &)g);
+}
+template <typename F>
+static hipError_t by_rows(const GeomS &f, const GeomS &c, F &&launch) {
+  return f.hx || c.hx ? launch(f, c) : launch((const Geom &)f, (const Geom &)c);
+}
+#define SBM_ROWS(g) std::decay_t<decltype(g)>
 
 static int fill_blocks(int64_t n) {
   const int64_t b = (n + kBlock - 1) / kBlock;
@@ -1293,16 +1349,22 @@ hipError_t launch_residual(const Level &L, const T *psi, const Coef<T> &C, const
   const int bs = partials ? kBlock : level_block(L.g.nn);
   const int nb = partials ? grid_blocks(L.g.nn) : level_grid(L.g.nn);
   if (L.g.dim == 3) {
-    if (cls) SBM_LAUNCH((k_residual<T, 3, true>), nb, bs, st, L.g, C, psi, u, f, r, partials, cls);
-    SBM_LAUNCH((k_residual<T, 3, false>), nb, bs, st, L.g, C, psi, u, f, r, partials, cls);
+    if (cls)
+      SBM_LAUNCH((k_residual<T, 3, true, Geom>), nb, bs, st, L.g, C, psi, u, f, r, partials, cls);
+    return by_rows(L.g, [&](const auto &g) {
+      SBM_LAUNCH((k_residual<T, 3, false, SBM_ROWS(g)>), nb, bs, st, g, C, psi, u, f, r, partials,
+                 cls);
+    });
   }
-  if (cls) SBM_LAUNCH((k_residual<T, 2, true>), nb, bs, st, L.g, C, psi, u, f, r, partials, cls);
-  SBM_LAUNCH((k_residual<T, 2, false>), nb, bs, st, L.g, C, psi, u, f, r, partials, cls);
+  if (cls) SBM_LAUNCH((k_residual<T, 2, true, Geom>), nb, bs, st, L.g, C, psi, u, f, r, partials, cls);
+  SBM_LAUNCH((k_residual<T, 2, false, Geom>), nb, bs, st, L.g, C, psi, u, f, r, partials, cls);
 }
 
 hipError_t launch_residual_sweep(const Level &L, const double *u, const double *f,
                                  double *u_out, double omega, int colour, double *partials,
                                  hipStream_t st) {
+  if (L.g.hx)  // split rows: only the relaxed colour is written
+    return launch_residual_sweep_tiled(L, u, f, u_out, omega, colour, partials, st);
   if (use_tiled(L)) return hipErrorInvalidValue;  // partials are counted per node block
   if (L.g.dim == 3)
     SBM_LAUNCH((k_residual_sweep<3>), grid_blocks(L.g.nn), kBlock, st, L.g, L.c64, L.psi64, u, f,
@@ -1324,17 +1386,18 @@ hipError_t launch_jacobi(const Level &L, const T *psi, const Coef<T> &C, const T
                          T *u_out, double omega, hipStream_t st, const uint8_t *cls) {
   const int nb = level_grid(L.g.nn), bs = level_block(L.g.nn);
   if (L.g.dim == 3) {
-    if (cls) SBM_LAUNCH((k_jacobi<T, 3, true>), nb, bs, st, L.g, C, psi, u, f, u_out, (T)omega, cls);
-    SBM_LAUNCH((k_jacobi<T, 3, false>), nb, bs, st, L.g, C, psi, u, f, u_out, (T)omega, cls);
+    if (cls) SBM_LAUNCH((k_jacobi<T, 3, true, Geom>), nb, bs, st, L.g, C, psi, u, f, u_out, (T)omega, cls);
+    SBM_LAUNCH((k_jacobi<T, 3, false, Geom>), nb, bs, st, L.g, C, psi, u, f, u_out, (T)omega, cls);
   }
-  if (cls) SBM_LAUNCH((k_jacobi<T, 2, true>), nb, bs, st, L.g, C, psi, u, f, u_out, (T)omega, cls);
-  SBM_LAUNCH((k_jacobi<T, 2, false>), nb, bs, st, L.g, C, psi, u, f, u_out, (T)omega, cls);
+  if (cls) SBM_LAUNCH((k_jacobi<T, 2, true, Geom>), nb, bs, st, L.g, C, psi, u, f, u_out, (T)omega, cls);
+  SBM_LAUNCH((k_jacobi<T, 2, false, Geom>), nb, bs, st, L.g, C, psi, u, f, u_out, (T)omega, cls);
 }
 
 template <typename T>
 hipError_t launch_rb_half(const Level &L, const T *psi, const Coef<T> &C, const T *u,
                           const T *f, T *u_out, double omega, int colour, hipStream_t st,
                           const uint8_t *cls) {
+  if (L.g.hx) return hipErrorInvalidValue;  // split rows: launch_rb_split
   const int64_t pairs = (int64_t)((L.g.nx + 1) / 2) * L.g.ny * L.g.nz;
   const int nb = level_grid(pairs), bs = level_block(pairs);
   if (L.g.dim == 3) {
@@ -1367,15 +1430,21 @@ hipError_t launch_restrict(const Level &F, const Level &Cl, const T *r, T *fc, h
     return hipGetLastError();
   }
   const int nb = level_grid(Cl.g.nn), bs = level_block(Cl.g.nn);
-  if (F.g.dim == 3) SBM_LAUNCH((k_restrict<T, 3>), nb, bs, st, F.g, Cl.g, r, fc, ec);
-  SBM_LAUNCH((k_restrict<T, 2>), nb, bs, st, F.g, Cl.g, r, fc, ec);
+  if (F.g.dim == 3)
+    return by_rows(F.g, Cl.g, [&](const auto &gf, const auto &gc) {
+      SBM_LAUNCH((k_restrict<T, 3, SBM_ROWS(gf)>), nb, bs, st, gf, gc, r, fc, ec);
+    });
+  SBM_LAUNCH((k_restrict<T, 2, Geom>), nb, bs, st, F.g, Cl.g, r, fc, ec);
 }
 
 template <typename T>
 hipError_t launch_prolong_add(const Level &F, const Level &Cl, const T *e, T *u, hipStream_t st) {
   const int nb = level_grid(Cl.g.nn), bs = level_block(Cl.g.nn);
-  if (F.g.dim == 3) SBM_LAUNCH((k_prolong_add<T, 3>), nb, bs, st, F.g, Cl.g, e, u);
-  SBM_LAUNCH((k_prolong_add<T, 2>), nb, bs, st, F.g, Cl.g, e, u);
+  if (F.g.dim == 3)
+    return by_rows(F.g, Cl.g, [&](const auto &gf, const auto &gc) {
+      SBM_LAUNCH((k_prolong_add<T, 3, SBM_ROWS(gf)>), nb, bs, st, gf, gc, e, u);
+    });
+  SBM_LAUNCH((k_prolong_add<T, 2, Geom>), nb, bs, st, F.g, Cl.g, e, u);
 }
 
 template <typename T>
@@ -1412,8 +1481,11 @@ hipError_t launch_copy(const T *src, T *dst, int64_t n, hipStream_t st) {
 
 hipError_t launch_correct(const Level &L, double *u, const float *e32, const double *ss,
                           hipStream_t st) {
-  if (L.g.dim == 3) SBM_LAUNCH((k_correct<3>), num_blocks(L.g.nn), kBlock, st, L.g, u, e32, ss);
-  SBM_LAUNCH((k_correct<2>), num_blocks(L.g.nn), kBlock, st, L.g, u, e32, ss);
+  if (L.g.dim == 3)
+    return by_rows(L.g, [&](const auto &g) {
+      SBM_LAUNCH((k_correct<3, SBM_ROWS(g)>), num_blocks(L.g.nn), kBlock, st, g, u, e32, ss);
+    });
+  SBM_LAUNCH((k_correct<2, Geom>), num_blocks(L.g.nn), kBlock, st, L.g, u, e32, ss);
 }
 
 hipError_t launch_set_dirichlet(const Level &L, double *u, const DispValues &dv, hipStream_t st) {
@@ -1440,6 +1512,25 @@ hipError_t launch_rhs(const Level &L, const Traction &tr, const double *b, doubl
   SBM_LAUNCH((k_rhs<2>), num_blocks(L.g.nn), kBlock, st, L.g, tr, L.psi64, b, fA, flag);
 }
 
+hipError_t launch_take_load(const Level &L, const double *f, double *out, double *partials,
+                            hipStream_t st) {
+  if (L.g.dim == 3)
+    SBM_LAUNCH((k_take_load<3>), num_blocks(L.g.nn), kBlock, st, L.g, L.g.hx, f, out, partials);
+  SBM_LAUNCH((k_take_load<2>), num_blocks(L.g.nn), kBlock, st, L.g, L.g.hx, f, out, partials);
+}
+
+template <typename T>
+hipError_t launch_to_split(const Level &L, const T *src, T *dst, hipStream_t st) {
+  if (!L.g.hx) return launch_copy<T>(src, dst, (int64_t)L.g.dim * L.g.nn, st);
+  SBM_LAUNCH((k_relayout<T, true>), num_blocks(L.g.nn), kBlock, st, L.g, L.g.dim, L.g.hx, src, dst);
+}
+template <typename T>
+hipError_t launch_from_split(const Level &L, const T *src, T *dst, hipStream_t st) {
+  if (!L.g.hx) return launch_copy<T>(src, dst, (int64_t)L.g.dim * L.g.nn, st);
+  SBM_LAUNCH((k_relayout<T, false>), num_blocks(L.g.nn), kBlock, st, L.g, L.g.dim, L.g.hx, src,
+             dst);
+}
+
 hipError_t launch_check_diag(const Level &L, int *flag, hipStream_t st) {
   if (L.g.dim == 3) SBM_LAUNCH((k_check_diag<3>), num_blocks(L.g.nn), kBlock, st, L.g, L.psi64, flag);
   SBM_LAUNCH((k_check_diag<2>), num_blocks(L.g.nn), kBlock, st, L.g, L.psi64, flag);
@@ -1451,8 +1542,11 @@ hipError_t launch_finalize_sum(const double *partials, int n, double *out, hipSt
 
 hipError_t launch_dot_free(const Level &L, const double *a, const ZSrc &b, double *partials,
                            hipStream_t st) {
-  if (L.g.dim == 3) SBM_LAUNCH((k_dot_free<3>), num_blocks(L.g.nn), kBlock, st, L.g, a, b, partials);
-  SBM_LAUNCH((k_dot_free<2>), num_blocks(L.g.nn), kBlock, st, L.g, a, b, partials);
+  if (L.g.dim == 3)
+    return by_rows(L.g, [&](const auto &g) {
+      SBM_LAUNCH((k_dot_free<3, SBM_ROWS(g)>), num_blocks(L.g.nn), kBlock, st, g, a, b, partials);
+    });
+  SBM_LAUNCH((k_dot_free<2, Geom>), num_blocks(L.g.nn), kBlock, st, L.g, a, b, partials);
 }
 
 hipError_t launch_apply_dot(const Level &L, const double *p, double *q, double *partials,
@@ -1467,25 +1561,29 @@ hipError_t launch_cg_update_r(const Level &L, double *r, const double *q, const 
                               const double *rz, const double *pq, double *alpha_out, double *pr,
                               double *pz, hipStream_t st, float *r32, const double *ss) {
   if (L.g.dim == 3)
-    SBM_LAUNCH((k_cg_update_r<3>), num_blocks(L.g.nn), kBlock, st, L.g, r, q, z, rz, pq,
-               alpha_out, pr, pz, r32, ss);
-  SBM_LAUNCH((k_cg_update_r<2>), num_blocks(L.g.nn), kBlock, st, L.g, r, q, z, rz, pq, alpha_out,
-             pr, pz, r32, ss);
+    return by_rows(L.g, [&](const auto &g) {
+      SBM_LAUNCH((k_cg_update_r<3, SBM_ROWS(g)>), num_blocks(L.g.nn), kBlock, st, g, r, q, z, rz, pq, alpha_out, pr, pz, r32, ss);
+    });
+  SBM_LAUNCH((k_cg_update_r<2, Geom>), num_blocks(L.g.nn), kBlock, st, L.g, r, q, z, rz, pq, alpha_out, pr, pz, r32, ss);
 }
 
 hipError_t launch_xpby_x(const Level &L, double *x, double *p, const ZSrc &z,
                          const double *rznew, const double *rzold, const double *rz,
                          const double *alpha, hipStream_t st) {
   if (L.g.dim == 3)
-    SBM_LAUNCH((k_xpby_x<3>), num_blocks(L.g.nn), kBlock, st, L.g, x, p, z, rznew, rzold, rz,
-               alpha);
-  SBM_LAUNCH((k_xpby_x<2>), num_blocks(L.g.nn), kBlock, st, L.g, x, p, z, rznew, rzold, rz, alpha);
+    return by_rows(L.g, [&](const auto &g) {
+      SBM_LAUNCH((k_xpby_x<3, SBM_ROWS(g)>), num_blocks(L.g.nn), kBlock, st, g, x, p, z, rznew, rzold, rz, alpha);
+    });
+  SBM_LAUNCH((k_xpby_x<2, Geom>), num_blocks(L.g.nn), kBlock, st, L.g, x, p, z, rznew, rzold, rz, alpha);
 }
 
 hipError_t launch_axpy_free(const Level &L, double *x, const double *p, const double *alpha,
                             hipStream_t st) {
-  if (L.g.dim == 3) SBM_LAUNCH((k_axpy_free<3>), num_blocks(L.g.nn), kBlock, st, L.g, x, p, alpha);
-  SBM_LAUNCH((k_axpy_free<2>), num_blocks(L.g.nn), kBlock, st, L.g, x, p, alpha);
+  if (L.g.dim == 3)
+    return by_rows(L.g, [&](const auto &g) {
+      SBM_LAUNCH((k_axpy_free<3, SBM_ROWS(g)>), num_blocks(L.g.nn), kBlock, st, g, x, p, alpha);
+    });
+  SBM_LAUNCH((k_axpy_free<2, Geom>), num_blocks(L.g.nn), kBlock, st, L.g, x, p, alpha);
 }
 
 
@@ -1520,13 +1618,47 @@ __global__ __launch_bounds__(kBlock) void k_zero_sweep(Geom g, Coef<T> C, const 
   }
 }
 
-hipError_t launch_zero_sweep(const Level &L, const double *f, double *t, double omega, int colour,
-                             hipStream_t st) {
+// The same on split rows: a thread per node of the colour, which alone is
+// written (its values are whole half rows).  Bound by memory: psi, half of f and
+// half of t, 32 B per node in FP64 (257^3: 146 us, FP32 85 us; a thread per node
+// with every other half row idle took 174 and 157 us).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_zero_split(GeomS g, Coef<T> C,
+                                                       const T *__restrict__ psi,
+                                                       const T *__restrict__ f, T *__restrict__ t,
+                                                       T omega, int colour) {
+  const int64_t tid = (int64_t)xcd_block() * kBlock + threadIdx.x;
+  if (tid >= (int64_t)g.hx * g.ny * g.nz) return;
+  const uint32_t rest = g.fpx.div((uint32_t)tid);
+  const int p = (int)((uint32_t)tid - rest * (uint32_t)g.hx);
+  const int k = (int)g.fny.div(rest);
+  const int j = (int)(rest - (uint32_t)k * (uint32_t)g.ny);
+  const int i = 2 * p + ((colour + j + k) & 1);
+  if (i >= g.nx) return;
+  const int64_t id = split_x(g.hx, i) + (int64_t)g.nx * rest;
+  T fv[3], dg[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) fv[c] = f[c * g.nn + id];
+  node_diag<T, 3>(g, C, psi, i, j, k, dg);
+  const uint32_t fb = face_bits(g, i, j, k);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const T w = ((g.dmask >> c) & fb) ? T(0) : omega;
+    t[c * g.nn + id] = T(0) + w * (fv[c] - T(0)) / dg[c];
+  }
+}
+
+template <typename T>
+hipError_t launch_zero_sweep(const Level &L, const T *psi, const Coef<T> &C, const T *f, T *t,
+                             double omega, int colour, hipStream_t st) {
+  if (L.g.hx)
+    SBM_LAUNCH((k_zero_split<T>), grid_blocks((int64_t)L.g.hx * L.g.ny * L.g.nz), kBlock, st, L.g, C,
+               psi, f, t, (T)omega, colour);
   if (L.g.dim == 3)
-    SBM_LAUNCH((k_zero_sweep<double, 3>), grid_blocks(L.g.nn), kBlock, st, L.g, L.c64, L.psi64, f,
-               t, omega, colour);
-  SBM_LAUNCH((k_zero_sweep<double, 2>), grid_blocks(L.g.nn), kBlock, st, L.g, L.c64, L.psi64, f, t,
-             omega, colour);
+    SBM_LAUNCH((k_zero_sweep<T, 3>), grid_blocks(L.g.nn), kBlock, st, L.g, C, psi, f, t, (T)omega,
+               colour);
+  SBM_LAUNCH((k_zero_sweep<T, 2>), grid_blocks(L.g.nn), kBlock, st, L.g, C, psi, f, t, (T)omega,
+             colour);
 }
 
 hipError_t launch_scale_cast_sweep(const Level &L, const double *r, float *r32, float *t32,
@@ -1666,6 +1798,10 @@ hipError_t launch_sensitivity(const Level &L, double lam, double mu, const Tract
   template hipError_t launch_prolong_add<T>(const Level &, const Level &, const T *, T *,       \
                                             hipStream_t);                                      \
   template hipError_t launch_fill<T>(T *, int64_t, T, hipStream_t);                             \
+  template hipError_t launch_zero_sweep<T>(const Level &, const T *, const Coef<T> &, const T *, \
+                                           T *, double, int, hipStream_t);                      \
+  template hipError_t launch_to_split<T>(const Level &, const T *, T *, hipStream_t);           \
+  template hipError_t launch_from_split<T>(const Level &, const T *, T *, hipStream_t);         \
   template hipError_t launch_copy<T>(const T *, T *, int64_t, hipStream_t);                     \
   template hipError_t launch_bottom_cg<T>(const Level &, const T *, const Coef<T> &, const T *, \
                                           T *, T *, T *, T *, double, int, int *, hipStream_t);

@@ -75,6 +75,7 @@ struct sbm_ctx {
   DispValues zero_dv{};
   double fnorm = 0.0;
   int last_bottom_iters = 0;
+  bool fs_ok = false;  // L[0].fs holds the current load
   double *x0 = nullptr;  // finest-level iterate (fixed address for captured cycles)
   double *kr = nullptr, *kz = nullptr, *kp = nullptr, *kq = nullptr;  // flexible CG vectors
   // set while a CG preconditioner cycle is built: its last finest half-sweep
@@ -272,9 +273,14 @@ static size_t carve(sbm_ctx *c, char *base) {
   Carver cv{base};
   const int d = c->dim;
   int64_t maxblocks = 1;
+  // The half-sweep of levels with split rows reads psi up to 16 bytes before its
+  // start and vectors up to 64 bytes past their end (values that never count).
+  cv.take<char>(256);
   for (int l = 0; l < c->nlev; ++l) {
     Level &L = c->L[l];
     const int64_t nv = (int64_t)d * L.g.nn;
+    L.hx64 = l < c->nlev - 1 && split_level(L, false) ? (L.g.nx + 1) / 2 : 0;
+    L.hx32 = l < c->nlev - 1 && split_level(L, true) ? (L.g.nx + 1) / 2 : 0;
     L.psi64 = cv.take<double>(L.g.nc);
     L.psi32 = cv.take<float>(L.g.nc);
     L.e = cv.take<double>(nv);
@@ -283,6 +289,7 @@ static size_t carve(sbm_ctx *c, char *base) {
     L.e32 = cv.take<float>(nv);
     L.f32 = cv.take<float>(nv);
     L.t32 = cv.take<float>(nv);
+    if (l == 0 && L.hx64) L.fs = cv.take<double>(nv);
     maxblocks = std::max<int64_t>(maxblocks, grid_blocks(L.g.nn));
     maxblocks = std::max<int64_t>(maxblocks, num_blocks(L.g.nc));
   }
@@ -373,6 +380,71 @@ static hipError_t half_sweep(const Level &L, const T *psi, const Coef<T> &C, con
                      : launch_rb_half<T>(L, psi, C, src, f, dst, om, colour, st);
 }
 
+// The vectors of a solve's wide levels have split rows (sbm_device.h) while it
+// runs; everything else sees natural rows.  Gauss-Seidel only; and the mixed CG
+// stays with natural rows: its Krylov scalars follow the rounding of the FP32
+// cycle, and another order of that arithmetic moves its residual history by 1e-9
+// (129-node rows) where FP64 cycles move by 1e-16.
+struct RowsScope {
+  sbm_ctx *c;
+  explicit RowsScope(sbm_ctx *c_) : c(c_) {
+    if (c->opt.smoother != 0 || (c->opt.precision == 1 && c->opt.krylov == 1)) return;
+    for (Level &L : c->L) L.g.hx = c->opt.precision == 1 ? L.hx32 : L.hx64;
+  }
+  ~RowsScope() {
+    for (Level &L : c->L) L.g.hx = 0;
+  }
+};
+
+// nu Gauss-Seidel sweeps on a level with split rows.  A half-sweep writes its
+// colour into the buffer that does not hold it, so a sweep moves the whole state
+// from one buffer to the other.
+template <typename T>
+static hipError_t smooth_split(sbm_ctx *c, int l, T *x, const T *f, T *tmp, int nu, bool reverse,
+                               bool pre) {
+  Level &L = c->L[l];
+  const T *psi = Prec<T>::psi(L);
+  const Coef<T> &C = Prec<T>::coef(L);
+  const double om = opt_omega(c->opt);
+  const int c0 = reverse ? 1 : 0;
+  hipError_t e = hipSuccess;
+  // a correction that starts from zero (the finest level's when the caller says
+  // so, a coarser one's on its pre-smoothing)
+  const bool zero = (l == 0 && c->zero_start) || (l > 0 && pre);
+  // the convergence test may have made the first half-sweep (into tmp)
+  const bool first_done = l == 0 && c->first_half_done;
+  if (l == 0) c->zero_start = c->first_half_done = false;
+  if (zero && nu == 0) return launch_fill<T>(x, (int64_t)c->dim * L.g.nn, T(0), c->st);
+  T *cur = x, *oth = tmp;
+  for (int s = 0; s < nu; ++s) {
+    if (s == 0 && zero) {
+      // from zero, in place: the first colour pointwise, the second from it
+      if (nu % 2 == 0) std::swap(cur, oth);  // the remaining sweeps end in x
+      ProfScope ps(c, SBM_PROF_SWEEP0, l == 0);
+      if ((e = launch_zero_sweep<T>(L, psi, C, f, cur, om, c0, c->st)) != hipSuccess) return e;
+      if ((e = launch_rb_split<T>(L, psi, C, nullptr, cur, f, cur, om, 1 - c0, c->st)) !=
+          hipSuccess)
+        return e;
+      continue;
+    }
+    if (s > 0 || !first_done) {
+      ProfScope ps(c, SBM_PROF_SMOOTH, l == 0);
+      if ((e = launch_rb_split<T>(L, psi, C, cur, cur, f, oth, om, c0, c->st)) != hipSuccess)
+        return e;
+    }
+    // the last half-sweep of a CG preconditioner's cycle writes z (= x) and
+    // forms the partials of r . z (r = f) on the way
+    double *dot = (l == 0 && !pre && s == nu - 1) ? c->rz_partials : nullptr;
+    ProfScope ps(c, dot ? SBM_PROF_SMOOTH_DOT : SBM_PROF_SMOOTH, l == 0);
+    if ((e = launch_rb_split<T>(L, psi, C, cur, oth, f, oth, om, 1 - c0, c->st, dot)) !=
+        hipSuccess)
+      return e;
+    std::swap(cur, oth);
+  }
+  if (cur != x) return launch_copy<T>(cur, x, (int64_t)c->dim * L.g.nn, c->st);
+  return hipSuccess;
+}
+
 // nu sweeps on level l for x with load f; tmp is the ping-pong buffer.
 template <typename T>
 static hipError_t smooth(sbm_ctx *c, int l, T *x, const T *f, T *tmp, int nu, bool reverse,
@@ -392,6 +464,7 @@ static hipError_t smooth(sbm_ctx *c, int l, T *x, const T *f, T *tmp, int nu, bo
     if (src != x) e = launch_copy<T>(src, x, (int64_t)c->dim * L.g.nn, c->st);
     return e;
   }
+  if (L.g.hx) return smooth_split<T>(c, l, x, f, tmp, nu, reverse, pre);
   const int c0 = reverse ? 1 : 0;
   // the finest level starts from zero when the caller says so (zero_start);
   // a coarser level always does on its pre-smoothing (its correction is the
@@ -477,10 +550,11 @@ static bool cast_fused(const sbm_ctx *c) {
 // the mixed cycle the FP32 half-sweep reads the FP64 residual for it).
 static bool rz_fused(const sbm_ctx *c) {
   const Level &L0 = c->L[0];
-  const bool fp32 = c->opt.precision == 1;
-  return c->opt.smoother == 0 && c->opt.nu_post >= 1 && c->nlev > 1 &&
-         (fp32 ? c->tail32 : c->tail64) != 0 && c->opt.fused_sweep != 1 && tiled_ok(L0) &&
-         rb_tiled_partials(L0, fp32) <= c->npart;
+  if (c->opt.smoother != 0 || c->opt.nu_post < 1 || c->nlev <= 1) return false;
+  if (c->opt.precision == 1)
+    return c->tail32 != 0 && c->opt.fused_sweep != 1 && tiled_ok(L0) &&
+           rb_tiled_partials(L0) <= c->npart;
+  return c->tail64 != 0 && L0.g.hx != 0 && rb_split_partials(L0) <= c->npart;
 }
 
 // Arms (ss: the mixed cast's squared scale; fp64: the FP64 cycle) or
@@ -647,7 +721,7 @@ static hipError_t cycle_body(sbm_ctx *c, const double *f, int mode) {
     // the tail, its first half-sweep from zero is pointwise (omega kr / D on
     // one colour) and is made together with the cast or instead of the fill.
     const bool skip = c->opt.smoother == 0 && c->opt.nu_pre >= 1 && c->nlev > 1;
-    // a finest level swept by the fused kernel starts that sweep from zero
+    // mixed: a tiled finest level starts with the one-launch sweep from zero
     const bool zs = skip && tiled_ok(L0);
     if (c->opt.precision == 1) {
       if (zs && c->tail32 != 0) {
@@ -672,10 +746,11 @@ static hipError_t cycle_body(sbm_ctx *c, const double *f, int mode) {
       // and scale it themselves (the FP64 z is never written)
       return launch_store_sqrt(c->scal, c->scal + 6, c->st);
     }
-    if (zs && c->tail64 != 0) {
+    if (L0.g.hx && skip && c->tail64 != 0) {
       c->zero_start = true;
     } else if (skip && c->tail64 != 0) {
-      if ((e = launch_zero_sweep(L0, c->kr, L0.t, opt_omega(c->opt), 0, c->st)) != hipSuccess)
+      if ((e = launch_zero_sweep<double>(L0, L0.psi64, L0.c64, c->kr, L0.t, opt_omega(c->opt), 0,
+                                         c->st)) != hipSuccess)
         return e;
       c->first_half_done = true;
     } else if ((e = launch_fill<double>(c->kz, nv, 0.0, c->st)) != hipSuccess) {
@@ -816,19 +891,18 @@ static sbm_status fin_to_host(sbm_ctx *c, const double *partials, int n, int slo
 static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double *u, double *hist,
                                int cap, int *ncyc, double *final_rel) {
   Level &L0 = c->L[0];
-  const int64_t nv = (int64_t)c->dim * L0.g.nn;
   const int nb = num_blocks(L0.g.nn);       // node-parallel kernels
   const int ns = stencil_partials(L0);      // residual / Apply kernels
   // r . z from the preconditioner's last half-sweep, else a pass of its own
   const bool rzf = rz_fused(c);
   const bool castf = cast_fused(c);
-  const int nrz = rzf ? rb_tiled_partials(L0, c->opt.precision == 1) : 0;
+  const int nrz = !rzf ? 0 : c->opt.precision == 1 ? rb_tiled_partials(L0) : rb_split_partials(L0);
   double rho_min = INFINITY, rho = 0.0;
   sbm_status status = SBM_NOT_CONVERGED;
   // the preconditioned residual: kz, or (mixed) scal[6] * the FP32 correction
   const ZSrc z = c->opt.precision == 1 ? ZSrc{nullptr, L0.e32, c->scal + 6}
                                        : ZSrc{c->kz, nullptr, nullptr};
-  HIP_TRY(launch_copy<double>(u, c->x0, nv, c->st));
+  HIP_TRY(launch_to_split<double>(L0, u, c->x0, c->st));
   {
     ProfScope ps(c, SBM_PROF_NORM, true);
     HIP_TRY((launch_residual<double>(L0, L0.psi64, L0.c64, c->x0, f, c->kr, c->partials, c->st)));
@@ -919,7 +993,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
   }
   if (ncyc) *ncyc = m;
   if (final_rel) *final_rel = rho;
-  HIP_TRY(launch_copy<double>(c->x0, u, nv, c->st));
+  HIP_TRY(launch_from_split<double>(L0, c->x0, u, c->st));
   HIP_TRY(hipStreamSynchronize(c->st));
   if (c->prof_on) prof_harvest(c);
   return status;
@@ -932,17 +1006,15 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
                              int cap, int *ncyc, double *final_rel) {
   if (c->opt.krylov == 1) return solve_krylov(c, f, fnorm, u, hist, cap, ncyc, final_rel);
   Level &L0 = c->L[0];
-  const int64_t nv = (int64_t)c->dim * L0.g.nn;
   double rho_min = INFINITY, rho = 0.0;
   int m = 0;
   sbm_status status = SBM_NOT_CONVERGED;
-  HIP_TRY(launch_copy<double>(u, c->x0, nv, c->st));
-  // FP64 V-cycles with Gauss-Seidel pre-smoothing on a finest level swept by
-  // the node-parallel kernels: the convergence test also makes the next
-  // cycle's first half-sweep (the iterate itself is left as it is, so a
+  HIP_TRY(launch_to_split<double>(L0, u, c->x0, c->st));
+  // FP64 V-cycles with Gauss-Seidel pre-smoothing: the convergence test also
+  // makes the next cycle's first half-sweep (the iterate itself is left as it is, so a
   // converged solve returns the tested iterate)
   const bool fused = c->opt.precision == 0 && c->opt.smoother == 0 && c->opt.nu_pre >= 1 &&
-                     c->nlev > 1 && c->tail64 != 0 && residual_sweep_ok(L0);
+                     c->nlev > 1 && c->tail64 != 0 && (L0.g.hx != 0 || residual_sweep_ok(L0));
   // mixed: the convergence test keeps f - K x0 for the cycle's cast, which
   // also makes the FP32 cycle's first half-sweep when the finest level
   // smooths outside the tail
@@ -985,7 +1057,7 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
   }
   if (ncyc) *ncyc = m;
   if (final_rel) *final_rel = rho;
-  HIP_TRY(launch_copy<double>(c->x0, u, nv, c->st));
+  HIP_TRY(launch_from_split<double>(L0, c->x0, u, c->st));
   HIP_TRY(hipStreamSynchronize(c->st));
   if (c->prof_on) prof_harvest(c);
   return status;
@@ -1277,6 +1349,7 @@ static sbm_status set_problem_impl(sbm_ctx *c, const double *psi_raw, int cube,
   HIP_TRY(hipStreamSynchronize(c->st));
   memcpy(&flags, c->host, sizeof(int));
   c->have_problem = false;
+  c->fs_ok = false;
   if (flags & 1) return fail(SBM_E_NONFINITE, "NaN/Inf in psi or body force");
   if (flags & 2) return fail(SBM_E_DIAG, "a free DOF has no solid cell around it (zero diagonal)");
   // fnorm = ||fA - K uD|| over free DOF (uD: prescribed values, 0 elsewhere)
@@ -1313,7 +1386,13 @@ sbm_status sbm_solve(sbm_ctx *c, double *u, double *hist, int cap, int *ncyc, do
   if (!u) return fail(SBM_E_ARG, "u is NULL");
   Level &L0 = c->L[0];
   HIP_TRY(launch_set_dirichlet(L0, u, c->dv, c->st));
-  return solve_impl(c, L0.f, c->fnorm, u, hist, cap, ncyc, final_rel);
+  const RowsScope rows(c);
+  if (!L0.g.hx) return solve_impl(c, L0.f, c->fnorm, u, hist, cap, ncyc, final_rel);
+  if (!c->fs_ok) {  // the load in the solve's rows, once per problem
+    HIP_TRY(launch_to_split<double>(L0, L0.f, L0.fs, c->st));
+    c->fs_ok = true;
+  }
+  return solve_impl(c, L0.fs, c->fnorm, u, hist, cap, ncyc, final_rel);
 }
 
 sbm_status sbm_solve_rhs(sbm_ctx *c, const double *g, double *x, double *hist, int cap, int *ncyc,
@@ -1321,15 +1400,14 @@ sbm_status sbm_solve_rhs(sbm_ctx *c, const double *g, double *x, double *hist, i
   NEED_PROBLEM(c);
   if (!g || !x) return fail(SBM_E_ARG, "NULL argument");
   Level &L0 = c->L[0];
-  const int64_t nv = (int64_t)c->dim * L0.g.nn;
-  // masked copy of g: r = g - K*0 on free DOF via the residual kernel
-  HIP_TRY(launch_fill<double>(L0.t, nv, 0.0, c->st));
-  HIP_TRY((launch_residual<double>(L0, L0.psi64, L0.c64, L0.t, g, L0.e, c->partials, c->st)));
-  HIP_TRY(launch_finalize_sum(c->partials, stencil_partials(L0), c->scal, c->st));
+  HIP_TRY(launch_set_dirichlet(L0, x, c->zero_dv, c->st));
+  const RowsScope rows(c);
+  // g on the free DOF in the solve's rows, and its norm
+  HIP_TRY(launch_take_load(L0, g, L0.e, c->partials, c->st));
+  HIP_TRY(launch_finalize_sum(c->partials, num_blocks(L0.g.nn), c->scal, c->st));
   HIP_TRY(hipMemcpyAsync(c->host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->st));
   HIP_TRY(hipStreamSynchronize(c->st));
   const double gn = sqrt(c->host[0]);
-  HIP_TRY(launch_set_dirichlet(L0, x, c->zero_dv, c->st));
   return solve_impl(c, L0.e, gn, x, hist, cap, ncyc, final_rel);
 }
 

@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "sbm_internal.h"
+#include "sbm_tile.h"
 
 namespace sbm {
 namespace {
@@ -27,22 +28,6 @@ constexpr int NT = TX / 2 * TY;             // threads: one x-pair per thread
 constexpr int PLANE = LY * LX;              // LDS entries per component and plane
 constexpr int NU = 3 * PLANE;
 constexpr int NUPT = (NU + NT - 1) / NT;
-
-// The level geometry the tiled kernels need (3D only; fewer scalar registers
-// than Geom).
-struct TG {
-  int nx, ny, nz, cx, cy, cz, nn;
-  uint32_t dmask;
-};
-
-TG make_tg(const Geom &g) { return TG{g.nx, g.ny, g.nz, g.cx, g.cy, g.cz, (int)g.nn, g.dmask}; }
-
-__device__ __forceinline__ bool tg_dirichlet(const TG &g, int i, int j, int k, int comp) {
-  const uint32_t m = g.dmask >> comp;
-  return ((i == 0) && (m & 1u)) || ((i == g.nx - 1) && ((m >> 3) & 1u)) ||
-         ((j == 0) && ((m >> 6) & 1u)) || ((j == g.ny - 1) && ((m >> 9) & 1u)) ||
-         ((k == 0) && ((m >> 12) & 1u)) || ((k == g.nz - 1) && ((m >> 15) & 1u));
-}
 
 // whole: a launch over the whole level -- the last node column / row of a
 // 2^n + 1 level go to node-parallel face blocks, and the z chunks are
@@ -65,35 +50,6 @@ enum class TileKind { half, zero, full };
 template <typename T>
 constexpr int tile_target(TileKind k) {
   return sizeof(T) != 8 ? 2048 : (k == TileKind::zero ? 1536 : 1792);
-}
-
-// Planes [k0, k1) of chunk tz.
-__device__ __forceinline__ void tile_chunk(const TileGeom &tg, int tz, int nz, int &k0, int &k1) {
-  if (tg.nzc > 0) {
-    k0 = tz * nz / tg.nzc;
-    k1 = (tz + 1) * nz / tg.nzc;
-  } else {
-    k0 = tz * tg.kz;
-    k1 = min(k0 + tg.kz, nz);
-  }
-}
-
-// Face node f of a launch with face blocks: the last column x = nx-1 (all
-// rows) first, then the last row y = ny-1 (the other columns), plane by plane.
-__device__ __forceinline__ bool face_node(const TG &g, const TileGeom &tg, int f, int &x, int &y,
-                                          int &z) {
-  const int per = (tg.xface ? g.ny : 0) + (tg.yface ? g.nx - tg.xface : 0);
-  if (f >= per * g.nz) return false;
-  z = f / per;
-  const int e = f - z * per;
-  if (tg.xface && e < g.ny) {
-    x = g.nx - 1;
-    y = e;
-  } else {
-    x = e - (tg.xface ? g.ny : 0);
-    y = g.ny - 1;
-  }
-  return true;
 }
 
 TileGeom tile_geom(const TG &g, bool whole, int kz_set, int target) {
@@ -124,37 +80,6 @@ TileGeom tile_geom(const TG &g, bool whole, int kz_set, int target) {
   t.kz = kz;
   t.ntiles = cols * ((g.nz + kz - 1) / kz);
   return t;
-}
-
-// ---------------------------------------------------------------- buffers
-//
-// The tiled kernels address u, f, psi and the outputs through raw buffer
-// descriptors: the per-thread byte offset within a plane (a VGPR computed once)
-// plus the plane's offset (an SGPR) is added by the memory unit, and an offset
-// at or past the buffer's size reads 0 and drops a store.  Halo entries
-// outside the box therefore load as the zeros eq. K needs there, with no
-// select per value, and a thread without a node stores nothing.  Offsets stay
-// below 2^31 (tiled_ok limits a level's vector to that many bytes).
-constexpr int kOOB = 0x7ffffff8;    // byte offset past every buffer
-constexpr int kRsrcW3 = 0x00020000; // descriptor word 3: 32-bit data format, raw access
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, bytes, kRsrcW3);
-}
-template <typename T>
-__device__ __forceinline__ T bload(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-  if constexpr (sizeof(T) == 8)
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
-  else
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-}
-typedef unsigned int u32x2 __attribute__((__vector_size__(2 * sizeof(unsigned int))));
-template <typename T>
-__device__ __forceinline__ void bstore(T v, __amdgpu_buffer_rsrc_t r, int voff, int soff) {
-  if constexpr (sizeof(T) == 8)
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
-  else
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
 }
 
 // ---------------------------------------------------------------- LDS tile
@@ -191,7 +116,8 @@ __device__ __forceinline__ void tile_slots(const TG &g, int x0, int y0, int (&vu
       const int y = r / LX, xr = r - y * LX;
       const int hf = xr >= HUX ? 1 : 0;
       const int gx = x0 - 1 + 2 * (xr - hf * HUX) + hf, gy = y0 - 1 + y;
-      if (gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny) vu[j] = (c * g.nn + gx + g.nx * gy) * W;
+      if (gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny)
+        vu[j] = (c * g.nn + split_x(g.hx, gx) + g.nx * gy) * W;
     }
   }
 #pragma unroll
@@ -301,26 +227,6 @@ __device__ __forceinline__ void tile_stencil(const CO &C, const T *Lm, const T *
   stencil3<T>(C, P, U, out, dg);
 }
 
-// Hardware block b of a launch over n listed (or all) tiles: the tiles first,
-// in the XCD-ordered numbering of the first n rounded up to 8 blocks (workgroup
-// b runs on XCD b mod 8; each XCD gets a contiguous range of tiles); the face
-// blocks of a whole-level launch last (short node-parallel blocks that fill
-// the slots the last tiles leave idle).  Returns the logical tile, or -1 - fb
-// for face block fb.
-__device__ __forceinline__ int tile_or_face(int n) {
-  const int n8 = (n + 7) / 8 * 8;
-  const int b = blockIdx.x;
-  if (b >= n8) return -1 - (b - n8);
-  return (b & 7) * (n8 >> 3) + (b >> 3);
-}
-
-// The FP64 residual an FP32 half-sweep with DOT reads instead of its load:
-// the load is r / s (s = sqrt(*ss)) formed as the mixed cast forms it, and the
-// sum is r . (s u_out), the CG's r . z with z = s e.
-struct DotSrc {
-  const double *r, *ss;
-};
-
 // A face node (last column / row of a 2^n + 1 level) of a whole-level tiled
 // half-sweep: one node per thread from global memory, the same update.  With
 // DOT the block's sum of f . u_out over free DOF goes to partials[ntiles + fb]
@@ -376,8 +282,10 @@ __device__ __forceinline__ void rb_face_node(const TG &g, const CO &C, const T *
 
 // Colour-synchronous Gauss-Seidel half-sweep (nodes with (x+y+z) mod 2 ==
 // colour updated from u, the others copied to u_out), as k_rb_half, over the
-// tiles and, in a whole-level launch, the face blocks.  With MASK only
-// class-1 nodes are updated.  A thread owns an x-pair (one node of each
+// tiles and, in a whole-level launch, the face blocks (natural rows: adaptive
+// levels, FP32 levels up to 192 nodes wide, the mixed CG and the component entry;
+// the others have split rows, sbm_split.hip).  With MASK only class-1 nodes are
+// updated.  A thread owns an x-pair (one node of each
 // colour) and stores both.  The u and psi planes of the next step and f of
 // the next plane are loaded while the current plane is computed.  With DOT
 // (a whole-level launch) each tile also sums f . u_out over its free DOF --
@@ -537,10 +445,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   }
 }
 
-// Where a residual pass writes fp32(r / s), s = sqrt(*ss) (MODE 2 below).
+// What a residual pass writes besides the norm: fp32(r / s), s = sqrt(*ss)
+// (MODE 2 below), or the half-sweep of one colour (MODE 3).
 struct CastOut {
-  float *r32;
-  const double *ss;
+  float *r32 = nullptr;
+  const double *ss = nullptr;
+  double *half = nullptr;
+  double omega = 0.0;
+  int colour = 0;
 };
 __device__ __forceinline__ double inv_sqrt(double ss) {
   const double s = sqrt(ss);
@@ -559,7 +471,7 @@ __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const 
   double acc = 0.0;
   int x, y, z;
   if (face_node(g, tg, fb * NT + (int)threadIdx.x, x, y, z)) {
-    const int q = x + g.nx * (y + g.ny * z);
+    const int q = split_x(g.hx, x) + g.nx * (y + g.ny * z);
     T v[3] = {T(0), T(0), T(0)};
     if (!(MASK && (cls[q] == 0 || cls[q] > 3))) {
       T out[3], dg[3], uc[3];
@@ -570,6 +482,8 @@ __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const 
         v[c] = tg_dirichlet(g, x, y, z, c) ? T(0) : val;
         if (MODE != 1) acc += (double)v[c] * (double)v[c];
         else acc += (double)uc[c] * (double)v[c];
+        if (MODE == 3 && ((x + y + z) & 1) == co.colour)
+          co.half[c * nn + q] = uc[c] + co.omega * v[c] / dg[c];
       }
     }
 #pragma unroll
@@ -593,7 +507,10 @@ __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const 
 //   MODE 2 (FP64, the mixed cycle's convergence test): as MODE 0 with partials,
 //     and the residual leaves as the FP32 cycle's load fp32(v / s) (CastOut)
 //     instead of r: 68 B per node, where the test and a second, node-parallel
-//     residual pass for the cast took 56 + 68 B and 831 us at 257^3 (339 us).
+//     residual pass for the cast took 56 + 68 B and 831 us at 257^3 (339 us);
+//   MODE 3 (FP64, split rows, the FP64 iteration's convergence test): as MODE 0
+//     with partials and without r, and the half-sweep of colour CastOut::colour
+//     from the same stencil values (relaxed nodes only, into CastOut::half).
 // Partials land in partials[tile], tiles in their logical order, then one per
 // face block (partials[ntiles + face block]).
 template <typename T, typename CO, int MODE, bool MASK>
@@ -615,8 +532,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   const int nn = g.nn, nxy = g.nx * g.ny;
   const int vbytes = 3 * nn * W;
   const TileBufs B{u, f, psi, vbytes, g.cx * g.cy * g.cz * W};
-  const __amdgpu_buffer_rsrc_t rout = MODE == 2 ? make_rsrc(co.r32, vbytes / 2)
-                                                : make_rsrc(r, r ? vbytes : 0);
+  const __amdgpu_buffer_rsrc_t rout = MODE == 2   ? make_rsrc(co.r32, vbytes / 2)
+                                      : MODE == 3 ? make_rsrc(co.half, vbytes)
+                                                  : make_rsrc(r, r ? vbytes : 0);
   const double inv_s = MODE == 2 ? inv_sqrt(*co.ss) : 0.0;
   const int tx = lt % tg.ntx, rest = lt / tg.ntx;
   const int ty = rest % tg.nty, tz = rest / tg.nty;
@@ -628,8 +546,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   const int yl = threadIdx.x / (TX / 2), p = threadIdx.x % (TX / 2);
   const int gy = y0 + yl;
   const int gx0 = x0 + 2 * p;  // the pair: gx0, gx0 + 1
-  const int vn[2] = {(gy < g.ny && gx0 < g.nx) ? (gy * g.nx + gx0) * W : kOOB,
-                     (gy < g.ny && gx0 + 1 < g.nx) ? (gy * g.nx + gx0 + 1) * W : kOOB};
+  const int vn[2] = {
+      (gy < g.ny && gx0 < g.nx) ? (gy * g.nx + split_x(g.hx, gx0)) * W : kOOB,
+      (gy < g.ny && gx0 + 1 < g.nx) ? (gy * g.nx + split_x(g.hx, gx0 + 1)) * W : kOOB};
   // f of both nodes, one plane ahead
   auto fetch_f = [&](int k, T (&fr)[2][3]) __attribute__((always_inline)) {
     if constexpr (MODE == 1) return;
@@ -695,6 +614,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
           v[c] = fixed ? T(0) : val;
           if (MODE != 1) acc += (double)v[c] * (double)v[c];
           else acc += (double)L0[c * PLANE + cu] * (double)v[c];
+          if constexpr (MODE == 3) v[c] = L0[c * PLANE + cu] + (T)co.omega * v[c] / dg[c];
         }
       }
       // without r the descriptor is empty and the stores are dropped (a branch
@@ -703,6 +623,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
       for (int c = 0; c < 3; ++c) {
         if constexpr (MODE == 2)  // FP32: half the byte offsets (kOOB / 2 is past the end too)
           bstore<float>((float)(v[c] * inv_s), rout, vn[h] >> 1, (so + c * nn * W) >> 1);
+        else if constexpr (MODE == 3)
+          bstore<T>(v[c], rout, ((gx + gy + k) & 1) == co.colour ? vn[h] : kOOB, so + c * nn * W);
         else
           bstore<T>(v[c], rout, vn[h], so + c * nn * W);
       }
@@ -1209,53 +1131,7 @@ __device__ __forceinline__ void zero_cells(const CO &C, const T *Pm, const T *P0
       P[0][b][a] = Pm[zcell(clx + a, cly + b)];
       P[1][b][a] = P0[zcell(clx + a, cly + b)];
     }
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    E[0][s] = P[0][0][s] + P[0][1][s] + P[1][0][s] + P[1][1][s];
-    E[1][s] = P[0][s][0] + P[0][s][1] + P[1][s][0] + P[1][s][1];
-    E[2][s] = P[s][0][0] + P[s][0][1] + P[s][1][0] + P[s][1][1];
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c)
-    dg[c] = coef_cd(C, c, 0) * (E[0][0] + E[0][1]) + coef_cd(C, c, 1) * (E[1][0] + E[1][1]) +
-            coef_cd(C, c, 2) * (E[2][0] + E[2][1]);
-}
-
-// (K u)(n) at a node n whose centre and edge neighbours are 0: F[c][a][s] is
-// component c at the face neighbour n + (2s - 1) e_a.  The expressions are
-// stencil3's with the zero terms removed.
-template <typename T, typename CO>
-__device__ __forceinline__ void zero_face_stencil(const CO &C, const T (&P)[2][2][2],
-                                                  const T (&E)[3][2], const T (&F)[3][3][2],
-                                                  T out[3]) {
-#pragma unroll
-  for (int c = 0; c < 3; ++c)
-    out[c] = -(coef_cd(C, c, 0) * (E[0][1] * F[c][0][1] + E[0][0] * F[c][0][0]) +
-               coef_cd(C, c, 1) * (E[1][1] * F[c][1][1] + E[1][0] * F[c][1][0]) +
-               coef_cd(C, c, 2) * (E[2][1] * F[c][2][1] + E[2][0] * F[c][2][0]));
-#pragma unroll
-  for (int pl = 0; pl < 3; ++pl) {
-    const int a = (pl == 2) ? 1 : 0;
-    const int b = (pl == 0) ? 1 : 2;
-    const T cm = coef_cm(C, pl);
-    T ra = T(0), rb = T(0);
-#pragma unroll
-    for (int qa = 0; qa < 2; ++qa)
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
-        const int sa = 2 * qa - 1, sb = 2 * qb - 1;
-        T Fs;
-        if (pl == 0) Fs = P[0][qb][qa] + P[1][qb][qa];
-        else if (pl == 1) Fs = P[qb][0][qa] + P[qb][1][qa];
-        else Fs = P[qb][qa][0] + P[qb][qa][1];
-        const T w = (sa * sb > 0) ? Fs : -Fs;
-        // u_b(n + sb e_b) - u_b(n + sa e_a) and u_a(n + sa e_a) - u_a(n + sb e_b)
-        ra += w * (cm * (F[b][b][qb] - F[b][a][qa]));
-        rb += w * (cm * (F[a][a][qa] - F[a][b][qb]));
-      }
-    out[a] -= ra;
-    out[b] -= rb;
-  }
+  zero_diag<T>(C, P, E, dg);
 }
 
 template <typename T, typename CO>
@@ -1492,19 +1368,6 @@ bool tiled_sweep_ok(const Level &L) {
          3 * L.g.nn * (int64_t)sizeof(double) < (int64_t)kOOB;
 }
 
-// The level's coefficients as the 4 scalars of CoefCubic when its cells are
-// cubic (the same numbers, so the results are those of Coef).
-template <typename T>
-static bool cubic_coef(const Coef<T> &C, CoefCubic<T> &cc) {
-  cc = CoefCubic<T>{C.cd[0][0], C.cd[0][1], C.cp[0], C.cm[0]};
-  for (int i = 0; i < 3; ++i) {
-    if (C.cp[i] != cc.p || C.cm[i] != cc.m) return false;
-    for (int j = 0; j < 3; ++j)
-      if (C.cd[i][j] != (i == j ? cc.dd : cc.od)) return false;
-  }
-  return true;
-}
-
 TileGeom tile_geom_of(const Level &L, int kz) { return tile_geom(make_tg(L.g), false, kz); }
 
 bool zero_sweep_ok(const Level &L) {
@@ -1515,15 +1378,14 @@ bool zero_sweep_ok(const Level &L) {
          3 * L.g.nn * (int64_t)sizeof(double) < (int64_t)kOOB;
 }
 
-// Workgroups of a tiled launch over n tiles: the tiles rounded up to a
-// multiple of 8 (XCD order), then the face blocks of a whole-level launch.
-static int tiled_grid(int n, int nface) { return (n + 7) / 8 * 8 + nface; }
-
 template <typename T>
 hipError_t launch_rb_tiled(const Level &L, const T *psi, const Coef<T> &C, const T *u, const T *f,
                            T *u_out, double omega, int colour, hipStream_t st,
                            const uint8_t *cls, const TileList *tl, double *partials,
                            const double *r64, const double *ss) {
+  if (L.g.hx) return hipErrorInvalidValue;  // split rows: launch_rb_split
+  // the partials: whole-level FP32 launches, r . (s u_out) from the FP64 residual r64 and s^2 = *ss
+  if (partials && (cls || tl || sizeof(T) == 8 || !r64 || !ss)) return hipErrorInvalidValue;
   const TG gg = make_tg(L.g);
   const TileGeom tg =
       tile_geom(gg, tl == nullptr, tl ? tl->kz : 0, tile_target<T>(TileKind::half));
@@ -1532,39 +1394,35 @@ hipError_t launch_rb_tiled(const Level &L, const T *psi, const Coef<T> &C, const
   CoefCubic<T> cc;
   const bool cubic = cubic_coef(C, cc);
   (void)hipGetLastError();
-  // the partials: whole-level launches; FP32 ones sum r . (s u_out) from the
-  // FP64 residual r64 and s^2 = *ss
-  if (partials && (cls || tl || (sizeof(T) != 8 && (!r64 || !ss)))) return hipErrorInvalidValue;
   const DotSrc ds{r64, ss};
   const int nface = tl ? 0 : tg.nface;
   if (n + nface > 0) {
     const dim3 grid(tiled_grid(n, nface)), block(NT);
-    if (partials && cubic)
-      hipLaunchKernelGGL((k_rb_tile<T, CoefCubic<T>, false, true>), grid, block, 0, st, gg, cc,
-                         psi, u, f, u_out, (T)omega, colour, tg, cls, ids, n, partials, ds);
-    else if (partials)
-      hipLaunchKernelGGL((k_rb_tile<T, Coef<T>, false, true>), grid, block, 0, st, gg, C, psi,
-                         u, f, u_out, (T)omega, colour, tg, cls, ids, n, partials, ds);
-    else if (cls && cubic)
-      hipLaunchKernelGGL((k_rb_tile<T, CoefCubic<T>, true, false>), grid, block, 0, st, gg, cc,
-                         psi, u, f, u_out, (T)omega, colour, tg, cls, ids, n, partials, ds);
-    else if (cls)
-      hipLaunchKernelGGL((k_rb_tile<T, Coef<T>, true, false>), grid, block, 0, st, gg, C, psi,
-                         u, f, u_out, (T)omega, colour, tg, cls, ids, n, partials, ds);
-    else if (cubic)
-      hipLaunchKernelGGL((k_rb_tile<T, CoefCubic<T>, false, false>), grid, block, 0, st, gg, cc,
-                         psi, u, f, u_out, (T)omega, colour, tg, cls, ids, n, partials, ds);
-    else
-      hipLaunchKernelGGL((k_rb_tile<T, Coef<T>, false, false>), grid, block, 0, st, gg, C, psi,
-                         u, f, u_out, (T)omega, colour, tg, cls, ids, n, partials, ds);
+    auto go = [&](auto &&cf, auto mask, auto dot) {
+      hipLaunchKernelGGL(
+          (k_rb_tile<T, std::decay_t<decltype(cf)>, decltype(mask)::value, decltype(dot)::value>),
+          grid, block, 0, st, gg, cf, psi, u, f, u_out, (T)omega, colour, tg, cls, ids, n, partials,
+          ds);
+    };
+    const std::true_type yes{};
+    const std::false_type no{};
+    if constexpr (sizeof(T) == 4) {
+      if (partials) {
+        if (cubic) go(cc, no, yes);
+        else go(C, no, yes);
+        return hipGetLastError();
+      }
+    }
+    if (cls && cubic) go(cc, yes, no);
+    else if (cls) go(C, yes, no);
+    else if (cubic) go(cc, no, no);
+    else go(C, no, no);
   }
   return hipGetLastError();
 }
 
-int rb_tiled_partials(const Level &L, bool fp32) {
-  const TileGeom tg = tile_geom(make_tg(L.g), true, 0,
-                                fp32 ? tile_target<float>(TileKind::half)
-                                     : tile_target<double>(TileKind::half));
+int rb_tiled_partials(const Level &L) {
+  const TileGeom tg = tile_geom(make_tg(L.g), true, 0, tile_target<float>(TileKind::half));
   return tg.ntiles + tg.nface;
 }
 
@@ -1575,6 +1433,7 @@ hipError_t launch_rb_fused(const Level &L, const T *psi, const Coef<T> &C, const
   const TileGeom tg = tile_geom(gg);
   const int grid = (tg.ntiles + 7) / 8 * 8;
   (void)hipGetLastError();
+  if (L.g.hx) return hipErrorInvalidValue;  // natural rows only
   if (u) {
     hipLaunchKernelGGL((k_rb_fused<T, false>), dim3(grid), dim3(NT), 0, st, gg, C, psi, u, f,
                        u_out, (T)omega, first_colour, tg);
@@ -1627,7 +1486,7 @@ static void full_tiled(const Level &L, const T *psi, const Coef<T> &C, const T *
       hipLaunchKernelGGL((k_full_tile<T, std::decay_t<decltype(cf)>, MODE, decltype(mask)::value>),
                          grid, block, 0, st, gg, cf, psi, u, f, r, partials, tg, cls, ids, n, co);
     };
-    if constexpr (MODE != 2) {
+    if constexpr (MODE < 2) {
       if (cls && cubic) return go(cc, std::true_type{});
       if (cls) return go(C, std::true_type{});
     }
@@ -1660,6 +1519,19 @@ hipError_t launch_residual_cast_tiled(const Level &L, const double *u, const dou
   (void)hipGetLastError();
   full_tiled<double, 2>(L, L.psi64, L.c64, u, f, (double *)nullptr, partials, st, nullptr,
                         nullptr, CastOut{r32, ss});
+  return hipGetLastError();
+}
+
+hipError_t launch_residual_sweep_tiled(const Level &L, const double *u, const double *f,
+                                       double *half, double omega, int colour, double *partials,
+                                       hipStream_t st) {
+  (void)hipGetLastError();
+  CastOut co;
+  co.half = half;
+  co.omega = omega;
+  co.colour = colour;
+  full_tiled<double, 3>(L, L.psi64, L.c64, u, f, (double *)nullptr, partials, st, nullptr,
+                        nullptr, co);
   return hipGetLastError();
 }
 
