@@ -180,6 +180,9 @@ hipError_t launch_residual_tiled(const Level &L, const T *psi, const Coef<T> &C,
                                  const uint8_t *cls, const TileList *tl = nullptr);
 hipError_t launch_apply_dot_tiled(const Level &L, const double *p, double *q, double *partials,
                                   hipStream_t st);
+// K u at every node over the tiles (tiled_sweep_ok levels, natural rows).
+hipError_t launch_apply_tiled(const Level &L, const double *psi, const Coef<double> &C,
+                              const double *u, double *y, hipStream_t st);
 // Number of partial sums launch_residual / launch_apply_dot write for level L.
 int stencil_partials(const Level &L);
 // fc = R r (full weighting); with ec the coarse correction is zeroed too.

@@ -1425,13 +1425,16 @@ sbm_status sbm_residual(sbm_ctx *c, const double *u, double *r, double *norm_hos
   if (!u) return fail(SBM_E_ARG, "u is NULL");
   NO_ALIAS(u, r);
   Level &L0 = c->L[0];
-  if (!norm_host) {
-    if (!r) return fail(SBM_E_ARG, "r and norm_host both NULL");
-    HIP_TRY((launch_residual<double>(L0, L0.psi64, L0.c64, u, L0.f, r, nullptr, c->st)));
-    return SBM_OK;
-  }
-  HIP_TRY((launch_residual<double>(L0, L0.psi64, L0.c64, u, L0.f, r, c->partials, c->st)));
-  HIP_TRY(launch_finalize_sum(c->partials, stencil_partials(L0), c->scal, c->st));
+  // over the tiles from 97 nodes wide, as the Apply (129^3: 48 against 56 us)
+  const bool tiles = tiled_sweep_ok(L0) && tiled_partials(L0) <= c->npart;
+  double *part = norm_host ? c->partials : nullptr;
+  if (!norm_host && !r) return fail(SBM_E_ARG, "r and norm_host both NULL");
+  HIP_TRY((tiles ? launch_residual_tiled<double>(L0, L0.psi64, L0.c64, u, L0.f, r, part, c->st,
+                                                 nullptr, nullptr)
+                 : launch_residual<double>(L0, L0.psi64, L0.c64, u, L0.f, r, part, c->st)));
+  if (!norm_host) return SBM_OK;
+  HIP_TRY(launch_finalize_sum(c->partials, tiles ? tiled_partials(L0) : stencil_partials(L0),
+                              c->scal, c->st));
   HIP_TRY(hipMemcpyAsync(c->host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->st));
   HIP_TRY(hipStreamSynchronize(c->st));
   *norm_host = sqrt(c->host[0]);

@@ -466,6 +466,7 @@ __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const 
                                                 const T *f, T *r, double *partials,
                                                 const TileGeom &tg, const uint8_t *cls, int fb,
                                                 double *red, const CastOut &co) {
+  constexpr bool KU = MODE == 1 || MODE == 4;
   const int nn = g.nn;
   const double inv_s = MODE == 2 ? inv_sqrt(*co.ss) : 0.0;
   double acc = 0.0;
@@ -478,9 +479,9 @@ __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const 
       node_stencil<T, 3, true, TG, CO>(g, C, psi, u, x, y, z, out, dg, uc);
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const T val = MODE != 1 ? f[c * nn + q] - out[c] : out[c];
-        v[c] = tg_dirichlet(g, x, y, z, c) ? T(0) : val;
-        if (MODE != 1) acc += (double)v[c] * (double)v[c];
+        const T val = KU ? out[c] : f[c * nn + q] - out[c];
+        v[c] = MODE != 4 && tg_dirichlet(g, x, y, z, c) ? T(0) : val;
+        if (!KU) acc += (double)v[c] * (double)v[c];
         else acc += (double)uc[c] * (double)v[c];
         if (MODE == 3 && ((x + y + z) & 1) == co.colour)
           co.half[c * nn + q] = uc[c] + co.omega * v[c] / dg[c];
@@ -510,7 +511,8 @@ __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const 
 //     residual pass for the cast took 56 + 68 B and 831 us at 257^3 (339 us);
 //   MODE 3 (FP64, split rows, the FP64 iteration's convergence test): as MODE 0
 //     with partials and without r, and the half-sweep of colour CastOut::colour
-//     from the same stencil values (relaxed nodes only, into CastOut::half).
+//     from the same stencil values (relaxed nodes only, into CastOut::half);
+//   MODE 4 (the public Apply): r = K u at every node, displacement DOF too.
 // Partials land in partials[tile], tiles in their logical order, then one per
 // face block (partials[ntiles + face block]).
 template <typename T, typename CO, int MODE, bool MASK>
@@ -529,6 +531,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   if (li >= n) return;
   const int lt = ids ? ids[li] : li;
   constexpr int W = sizeof(T);
+  constexpr bool KU = MODE == 1 || MODE == 4;
   const int nn = g.nn, nxy = g.nx * g.ny;
   const int vbytes = 3 * nn * W;
   const TileBufs B{u, f, psi, vbytes, g.cx * g.cy * g.cz * W};
@@ -551,7 +554,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
       (gy < g.ny && gx0 + 1 < g.nx) ? (gy * g.nx + split_x(g.hx, gx0 + 1)) * W : kOOB};
   // f of both nodes, one plane ahead
   auto fetch_f = [&](int k, T (&fr)[2][3]) __attribute__((always_inline)) {
-    if constexpr (MODE == 1) return;
+    if constexpr (KU) return;
     const __amdgpu_buffer_rsrc_t rf = make_rsrc(B.f, k < k1 ? vbytes : 0);
     const int so = k * nxy * W;
 #pragma unroll
@@ -583,7 +586,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) fv[h][c] = MODE != 1 ? FN[h][c] : T(0);
+      for (int c = 0; c < 3; ++c) fv[h][c] = KU ? T(0) : FN[h][c];
     const int clk[2] = {CLN[0], CLN[1]};
     tile_fetch_u<T>(g, B, vu, k + 2, RU);
     tile_fetch_p<T>(g, B, vp, k + 1, RP);
@@ -609,11 +612,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
         const int cu = (yl + 1) * LX + lds_col(lx, HUX);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const bool fixed = face && tg_dirichlet(g, gx, gy, k, c);
-          const T val = MODE != 1 ? fv[h][c] - out[c] : out[c];
+          const bool fixed = MODE != 4 && face && tg_dirichlet(g, gx, gy, k, c);
+          const T val = KU ? out[c] : fv[h][c] - out[c];
           v[c] = fixed ? T(0) : val;
-          if (MODE != 1) acc += (double)v[c] * (double)v[c];
-          else acc += (double)L0[c * PLANE + cu] * (double)v[c];
+          if (!KU) acc += (double)v[c] * (double)v[c];
+          else if (MODE == 1) acc += (double)L0[c * PLANE + cu] * (double)v[c];
           if constexpr (MODE == 3) v[c] = L0[c * PLANE + cu] + (T)co.omega * v[c] / dg[c];
         }
       }
@@ -1361,9 +1364,10 @@ bool tiled_ok(const Level &L) {
 }
 
 bool tiled_sweep_ok(const Level &L) {
-  // the half-sweep alone: also from 97 nodes (129^3, whose vectors sit in the
-  // Infinity Cache: 41.2 us against 44.6 us for the node-parallel kernel in
-  // FP64, 27.5 us against 36.2 us in FP32)
+  // the half-sweep, and K u and the residual of a caller's field: also from 97
+  // nodes (the half-sweep at 129^3, whose vectors sit in the Infinity Cache:
+  // 41.2 us against 44.6 us for the node-parallel kernel in FP64, 27.5 us
+  // against 36.2 us in FP32)
   return L.g.dim == 3 && L.g.nx > 96 && L.g.ny > 3 * TY &&
          3 * L.g.nn * (int64_t)sizeof(double) < (int64_t)kOOB;
 }
@@ -1509,6 +1513,15 @@ hipError_t launch_apply_dot_tiled(const Level &L, const double *p, double *q, do
                                   hipStream_t st) {
   (void)hipGetLastError();
   full_tiled<double, 1>(L, L.psi64, L.c64, p, (const double *)nullptr, q, partials, st, nullptr,
+                        nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_apply_tiled(const Level &L, const double *psi, const Coef<double> &C,
+                              const double *u, double *y, hipStream_t st) {
+  if (L.g.hx) return hipErrorInvalidValue;  // a caller's vectors: natural rows
+  (void)hipGetLastError();
+  full_tiled<double, 4>(L, psi, C, u, (const double *)nullptr, y, nullptr, st, nullptr,
                         nullptr);
   return hipGetLastError();
 }

@@ -180,13 +180,13 @@ class Solver:
 
     def apply(self, u, out=None):
         u_t = self._dev(u, shape=(self.dim,) + self.node_shape)
-        out = self.new_nodes() if out is None else out
+        out = torch.empty_like(u_t) if out is None else out
         check(lib().sbm_apply(self._ctx, _ptr(u_t), _ptr(out)))
         return out
 
     def residual(self, u, want_r=True):
         u_t = self._dev(u, shape=(self.dim,) + self.node_shape)
-        r = self.new_nodes() if want_r else None
+        r = torch.empty_like(u_t) if want_r else None
         nrm = ctypes.c_double(0.0)
         check(lib().sbm_residual(self._ctx, _ptr(u_t), _ptr(r), ctypes.byref(nrm)))
         return r, nrm.value
