@@ -203,7 +203,7 @@ class Solver:
         u_t = self._dev(u, shape=(self.dim,) + self.node_shape)
         l_t = self._dev(lam, shape=(self.dim,) + self.node_shape)
         d_t = self._dev(design, shape=self.cell_shape)
-        g = self.new_cells()
+        g = torch.empty(self.cell_shape, dtype=torch.float64, device=self.device)
         check(lib().sbm_sensitivity(self._ctx, _ptr(u_t), _ptr(l_t), float(lam_scale), _ptr(d_t),
                                     int(chain), _ptr(g)))
         return g
