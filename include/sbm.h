@@ -262,6 +262,13 @@ sbm_status sbm_plastic_source(sbm_ctx *ctx, const double *eps_p, double *f);
 sbm_status sbm_return_map(sbm_ctx *ctx, const double *u, const sbm_j2 *mat, double *eps_p,
                           double *alpha, double *beta, int64_t *n_plastic_host);
 
+/* The same with the new state written to arrays of its own (each may be the
+ * array it is read from; no other aliasing). */
+sbm_status sbm_return_map_to(sbm_ctx *ctx, const double *u, const sbm_j2 *mat,
+                             const double *eps_p, const double *alpha, const double *beta,
+                             double *eps_p_out, double *alpha_out, double *beta_out,
+                             int64_t *n_plastic_host);
+
 /* ----------------------------------------------- diffuse traction -------
  * Sec. 2.1, eq. SBMLinearElasticity: a traction t0 on the (diffuse) surface
  * of the solid, extended along the normals across the diffuse band (t_hat,

@@ -286,8 +286,9 @@ hipError_t launch_tail(int dim, bool wide_bottom, const void *dev, size_t lds_by
 hipError_t launch_plastic_source(const Level &L, double lam, double mu, const double *eps_p,
                                  double *fp, hipStream_t st);
 hipError_t launch_return_map(const Level &L, double mu, double sigma_y, double hbar, double theta,
-                             const double *u, double *eps_p, double *alpha, double *beta,
-                             int *count, hipStream_t st);
+                             const double *u, const double *eps_p, const double *alpha,
+                             const double *beta, double *eps_out, double *alpha_out,
+                             double *beta_out, int *count, hipStream_t st);
 // Diffuse traction (sbm_traction.hip): f = t_hat |grad psi| + p grad psi at
 // every node of the finest grid, psi = max(psi_raw, floor); t_hat may be NULL.
 hipError_t launch_diffuse_traction(const Level &L, const double *psi_raw, double floor_,

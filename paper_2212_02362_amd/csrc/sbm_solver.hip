@@ -1483,9 +1483,20 @@ sbm_status sbm_plastic_source(sbm_ctx *c, const double *eps_p, double *f) {
 
 sbm_status sbm_return_map(sbm_ctx *c, const double *u, const sbm_j2 *mat, double *eps_p,
                           double *alpha, double *beta, int64_t *n_plastic) {
+  return sbm_return_map_to(c, u, mat, eps_p, alpha, beta, eps_p, alpha, beta, n_plastic);
+}
+
+sbm_status sbm_return_map_to(sbm_ctx *c, const double *u, const sbm_j2 *mat, const double *eps_p,
+                             const double *alpha, const double *beta, double *eps_p_out,
+                             double *alpha_out, double *beta_out, int64_t *n_plastic) {
   NEED_PROBLEM(c);
-  if (!u || !mat || !eps_p || !alpha || !beta) return fail(SBM_E_ARG, "NULL argument");
-  NO_ALIAS(u, eps_p, alpha, beta, n_plastic);
+  if (!u || !mat || !eps_p || !alpha || !beta || !eps_p_out || !alpha_out || !beta_out)
+    return fail(SBM_E_ARG, "NULL argument");
+  // an output may be its own input, nothing else
+  NO_ALIAS(u, eps_p_out, alpha_out, beta_out, n_plastic);
+  if (aliased({eps_p, alpha_out}) || aliased({eps_p, beta_out}) || aliased({alpha, eps_p_out}) ||
+      aliased({alpha, beta_out}) || aliased({beta, eps_p_out}) || aliased({beta, alpha_out}))
+    return fail(SBM_E_ARG, "an output buffer aliases an input or another output");
   if (c->dim != 3) return fail(SBM_E_SHAPE, "plastic strain: 3D grids only");
   if (!(mat->sigma_y >= 0.0) || !(mat->hbar >= 0.0) || !(mat->theta >= 0.0 && mat->theta <= 1.0) ||
       !isfinite(mat->sigma_y) || !isfinite(mat->hbar))
@@ -1494,7 +1505,7 @@ sbm_status sbm_return_map(sbm_ctx *c, const double *u, const sbm_j2 *mat, double
   int *cnt = n_plastic ? c->iflag + 12 : nullptr;
   if (cnt) HIP_TRY(launch_fill<int>(cnt, 1, 0, c->st));
   HIP_TRY(launch_return_map(L0, c->mat.mu, mat->sigma_y, mat->hbar, mat->theta, u, eps_p, alpha,
-                            beta, cnt, c->st));
+                            beta, eps_p_out, alpha_out, beta_out, cnt, c->st));
   if (n_plastic) {
     HIP_TRY(hipMemcpyAsync(c->host, cnt, sizeof(int), hipMemcpyDeviceToHost, c->st));
     HIP_TRY(hipStreamSynchronize(c->st));

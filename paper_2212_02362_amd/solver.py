@@ -213,7 +213,9 @@ class Solver:
         """Nodal load -div(psi C eps_p) of a cell plastic strain (3D; eps_p
         of shape (6, nz, ny, nx), components xx, yy, zz, yz, xz, xy)."""
         e_t = self._dev(eps_p, shape=(6,) + self.cell_shape)
-        out = self.new_nodes() if out is None else out
+        if out is None:
+            out = torch.empty((self.dim,) + self.node_shape, dtype=torch.float64,
+                              device=self.device)
         check(lib().sbm_plastic_source(self._ctx, _ptr(e_t), _ptr(out)))
         return out
 
@@ -222,21 +224,20 @@ class Solver:
         (eps_p, alpha, beta, number of yielding cells); with inplace=True the
         given device tensors (float64, contiguous) are updated and returned."""
         u_t = self._dev(u, shape=(self.dim,) + self.node_shape)
-        state = []
+        state, new = [], []
         for a, shp in ((eps_p, (6,) + self.cell_shape), (alpha, self.cell_shape),
                        (beta, (6,) + self.cell_shape)):
             t = self._dev(a, shape=shp)
             if inplace:
                 if t is not a:
                     raise ValueError("inplace needs contiguous float64 tensors on the solver's device")
-            else:
-                t = t.clone()
             state.append(t)
+            new.append(t if inplace else torch.empty_like(t))
         m = SbmJ2(float(sigma_y), float(hbar), float(theta))
         n = ctypes.c_int64(0)
-        check(lib().sbm_return_map(self._ctx, _ptr(u_t), ctypes.byref(m), _ptr(state[0]),
-                                   _ptr(state[1]), _ptr(state[2]), ctypes.byref(n)))
-        return state[0], state[1], state[2], int(n.value)
+        check(lib().sbm_return_map_to(self._ctx, _ptr(u_t), ctypes.byref(m),
+                                      *(_ptr(t) for t in state + new), ctypes.byref(n)))
+        return new[0], new[1], new[2], int(n.value)
 
     # ---------------------------------------------------- diffuse traction
     def diffuse_traction(self, psi_raw, psi_floor, t_hat=None, pressure=0.0, out=None):
