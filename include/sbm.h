@@ -311,6 +311,10 @@ typedef struct {
  * (SBM_E_ARG).  Async. */
 sbm_status sbm_crack_drive(sbm_ctx *ctx, const double *u, double *H, uint8_t *intact);
 
+/* The same with max(H, W0+) written to H_out (which may be H). */
+sbm_status sbm_crack_drive_to(sbm_ctx *ctx, const double *u, const double *H, double *H_out,
+                              uint8_t *intact);
+
 /* One explicit step c_out = c - dt M [g'(c) H - Gc (2 xi lap(c) + w'(c) /
  * (2 xi))], w = 1 - g, projected onto [0, 1] (the range of the crack field;
  * a NaN stays NaN), c_out = 1 where intact; lap is the cell Laplacian

@@ -82,6 +82,7 @@ SIGNATURES = {
     "sbm_return_map_to": (ctypes.c_int, [_P, _P, ctypes.POINTER(SbmJ2)] + [_P] * 6 + [_I64P]),
     "sbm_diffuse_traction": (ctypes.c_int, [_P, _P, ctypes.c_double, _P, ctypes.c_double, _P]),
     "sbm_crack_drive": (ctypes.c_int, [_P, _P, _P, _P]),
+    "sbm_crack_drive_to": (ctypes.c_int, [_P, _P, _P, _P, _P]),
     "sbm_phase_step": (ctypes.c_int, [_P, _P, _P, _P, ctypes.POINTER(SbmPf), _P, _P]),
     "sbm_profile": (ctypes.c_int, [_P, ctypes.c_int]),
     "sbm_graph_info": (ctypes.c_int, [_P, _I64P, _I64P]),

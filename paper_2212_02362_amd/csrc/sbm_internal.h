@@ -296,8 +296,8 @@ hipError_t launch_diffuse_traction(const Level &L, const double *psi_raw, double
 // Phase-field fracture (sbm_fracture.hip): crack driving force of every cell
 // (H <- max(H, W0+), intact <- W0+ < W0-) and one explicit Ginzburg-Landau
 // step of the crack field c (writing c1 and psi = g(c1) + eta).
-hipError_t launch_crack_drive(const Level &L, double lam, double mu, const double *u, double *H,
-                              uint8_t *intact, hipStream_t st);
+hipError_t launch_crack_drive(const Level &L, double lam, double mu, const double *u,
+                              const double *H, double *H_out, uint8_t *intact, hipStream_t st);
 hipError_t launch_phase_step(const Level &L, const double *c0, const double *H,
                              const uint8_t *intact, double Gc, double xi, double M, double dt,
                              double eta, double *c1, double *psi, hipStream_t st);

@@ -1528,13 +1528,17 @@ sbm_status sbm_diffuse_traction(sbm_ctx *c, const double *psi_raw, double psi_fl
 }
 
 sbm_status sbm_crack_drive(sbm_ctx *c, const double *u, double *H, uint8_t *intact) {
+  return sbm_crack_drive_to(c, u, H, H, intact);
+}
+
+sbm_status sbm_crack_drive_to(sbm_ctx *c, const double *u, const double *H, double *H_out,
+                              uint8_t *intact) {
   NEED_PROBLEM(c);
-  if (!u || !H || !intact) return fail(SBM_E_ARG, "NULL argument");
-  if ((const void *)u == (const void *)H || (const void *)u == (const void *)intact ||
-      (const void *)H == (const void *)intact)
+  if (!u || !H || !H_out || !intact) return fail(SBM_E_ARG, "NULL argument");
+  if (aliased({u, H_out, intact}) || aliased({H, intact}))
     return fail(SBM_E_ARG, "u, H and intact must not alias each other");
   Level &L0 = c->L[0];
-  HIP_TRY(launch_crack_drive(L0, c->mat.lambda, c->mat.mu, u, H, intact, c->st));
+  HIP_TRY(launch_crack_drive(L0, c->mat.lambda, c->mat.mu, u, H, H_out, intact, c->st));
   return SBM_OK;
 }
 

@@ -262,11 +262,11 @@ class Solver:
         h_t = self._dev(H, shape=self.cell_shape)
         if inplace and h_t is not H:
             raise ValueError("inplace needs a contiguous float64 tensor on the solver's device")
-        if not inplace:
-            h_t = h_t.clone()
+        h_new = h_t if inplace else torch.empty_like(h_t)
         intact = torch.empty(self.cell_shape, dtype=torch.uint8, device=self.device)
-        check(lib().sbm_crack_drive(self._ctx, _ptr(u_t), _ptr(h_t), _ptr(intact)))
-        return h_t, intact
+        check(lib().sbm_crack_drive_to(self._ctx, _ptr(u_t), _ptr(h_t), _ptr(h_new),
+                                       _ptr(intact)))
+        return h_new, intact
 
     def phase_step(self, c, H, intact, Gc, xi, M, dt, eta=1e-4, out=None):
         """One explicit Ginzburg-Landau step of the crack field; returns
