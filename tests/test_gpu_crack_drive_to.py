@@ -32,3 +32,35 @@ def test_crack_drive_into_other_array(ncell):
     P = lambda t: ctypes.c_void_p(t.data_ptr())
     for h, o, i in ((H, u, intact), (H, Hn, H), (H, Hn, Hn)):
         assert lib().sbm_crack_drive_to(S._ctx, P(u), P(h), P(o), P(i)) == -1
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e-5, 1e-140])
+def test_principal_strains(scale):
+    """Uniform strains: diagonal, with equal values, of rank one, nearly diagonal,
+    random.  Corner differences and the rotations err by a few ulp of the largest
+    entry: 1e-13 of the energy of the strain's norm."""
+    import numpy as np
+
+    from paper_2212_02362_amd import Solver
+    n = (2, 2, 2)
+    S = Solver(n, (1.0,) * 3)
+    lam, mu = 0.6, 0.4
+    S.set_problem(np.ones(n), lam, mu, 1e-3, np.array([[1] * 3] + [[0] * 3] * 5), np.zeros((6, 3)))
+    rng = np.random.default_rng(1)
+    one = np.ones((3, 3))
+    cases = [np.zeros((3, 3)), np.diag([1.0, -2.0, 3.0]), np.eye(3), one, -one,
+             np.eye(3) + 1e-9 * one, np.diag([1.0, 1e-9, 0.0]) + 1e-20 * one,
+             np.array([[0.0, 1.0, 0.0], [1.0, 0.0, 0.0], [0.0, 0.0, 0.0]]),
+             np.array([[0.0, 0.0, 1e-12], [0.0, 1.0, 0.0], [1e-12, 0.0, 0.0]])]
+    cases += [m + m.T for m in rng.standard_normal((8, 3, 3))]
+    x = np.stack(np.meshgrid(*[np.arange(3.0)] * 3, indexing="ij")[::-1])
+    for k, E in enumerate(cases):
+        say("principal strains", k, scale)
+        H, intact = S.crack_drive(np.tensordot(scale * E, x, 1), np.zeros(n))
+        e = np.linalg.eigvalsh(E)
+        p, m = np.maximum(e, 0), np.minimum(e, 0)
+        wp, wm = (0.5 * lam * v.sum() ** 2 + mu * (v ** 2).sum() for v in (p, m))
+        tol = 1e-13 * (lam + mu) * (E ** 2).sum()
+        assert np.abs(H.cpu().numpy() / scale ** 2 - wp).max() <= tol, (k, wp)
+        if abs(wp - wm) > 2 * tol:
+            assert (intact.cpu().numpy() == (wp < wm)).all(), k
