@@ -269,14 +269,23 @@ constexpr int kTailMaxLevels = 6;
 constexpr size_t kTailArgBytes = 4096;
 constexpr size_t kTailDenseBytes = 64 * 64 * sizeof(double);
 constexpr int kTailWaveBottom = 64;  // bottoms up to this many nodes are solved in one wave
+// Bottoms of up to this many DOF (displacement DOF included) have their inverse
+// applied by the FP64 tail (see tail_inverse).
+constexpr int kTailInverse = 512;
 struct TailOpts {
   int nu_pre, nu_post, jacobi, reverse;
   double omega, rtol;
   int maxit;
+  int inverse;  // FP64: apply the inverse of tail_inverse (unless it flagged itself)
 };
 int tail_level(const std::vector<Level> &L, int precision, size_t lds_max);
 hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void *dev,
-                       double *dense_A, size_t lds_max, size_t *lds_bytes, hipStream_t st);
+                       double *dense_A, double *inv, int *inv_bad, size_t lds_max,
+                       size_t *lds_bytes, hipStream_t st);
+// The inverse of the bottom operator (FP64 tail; inv of tail_upload, (DOF)^2), a
+// column per workgroup by the bottom CG to a relative residual of tol; *inv_bad (0
+// on entry) is set when a column misses it.
+hipError_t tail_inverse(const Level &B, const void *dev, double tol, int maxit, hipStream_t st);
 template <typename T>
 hipError_t launch_tail(int dim, bool wide_bottom, const void *dev, size_t lds_bytes,
                        T *x, const T *f, const TailOpts &o, int *iters, hipStream_t st);

@@ -118,6 +118,8 @@ struct sbm_ctx {
   int tail64 = -1, tail32 = -1;
   char *tail_args = nullptr;
   double *tail_A = nullptr;  // dense bottom matrix of the tails
+  double *tail_inv = nullptr;  // inverse of the bottom operator (FP64 tail), flag in iflag[13]
+  bool inv_ready = false;      // it is that of the current problem and options
   size_t tail_lds64 = 0, tail_lds32 = 0;
   size_t tail_lds_max = 64 * 1024;  // LDS bytes a workgroup may hold on this device
   // set while a cycle runs whose first finest-level half-sweep was already
@@ -312,6 +314,7 @@ static size_t carve(sbm_ctx *c, char *base) {
   c->b_r64 = cv.take<double>(nb);
   c->tail_args = cv.take<char>(2 * (int64_t)kTailArgBytes);
   c->tail_A = cv.take<double>((int64_t)(kTailDenseBytes / sizeof(double)));
+  c->tail_inv = cv.take<double>(nb <= kTailInverse ? nb * nb : 0);
   return cv.off + 256;
 }
 
@@ -579,6 +582,26 @@ static hipError_t bottom32(sbm_ctx *c, const float *f, float *x) {
                              c->opt.bottom_rtol, bottom_maxit(c), c->iflag + 4, c->st);
 }
 
+// The bottom's inverse for the FP64 tail, once per problem before its first cycle:
+// as many CG solves as DOF side by side, where each cycle would make one (a 112-node
+// bottom: 247 us once against 215 us per cycle).  Where bottom_rtol is near its default 1e-12 and its iterations are not capped;
+// columns are solved to 1e-2 bottom_rtol, so a sum over 512 of them keeps
+// bottom_rtol.  A looser CG is cheaper and stays.
+static hipError_t prepare_inverse(sbm_ctx *c) {
+  const Level &B = c->L.back();
+  if (c->inv_ready || c->opt.precision != 0 || c->tail64 < 0 || c->opt.bottom_max_iter > 0 ||
+      !(c->opt.bottom_rtol >= 1e-13 && c->opt.bottom_rtol <= 1e-12) ||
+      c->dim * B.g.nn > kTailInverse)
+    return hipSuccess;
+  hipError_t e = launch_fill<int>(c->iflag + 13, 1, 0, c->st);
+  if (e != hipSuccess) return e;
+  if ((e = tail_inverse(B, c->tail_args, 1e-2 * c->opt.bottom_rtol, 2 * bottom_maxit(c),
+                        c->st)) != hipSuccess)
+    return e;
+  c->inv_ready = true;
+  return hipSuccess;
+}
+
 // V-cycle on level l: x (in/out), f (load), tmp (scratch of level l).
 template <typename T>
 static hipError_t vcycle(sbm_ctx *c, int l, T *x, const T *f, T *tmp) {
@@ -587,7 +610,7 @@ static hipError_t vcycle(sbm_ctx *c, int l, T *x, const T *f, T *tmp) {
     // the rest of the cycle in one workgroup (LDS-resident levels)
     ProfScope ps(c, SBM_PROF_BOTTOM, true);
     const TailOpts o{c->opt.nu_pre, c->opt.nu_post, c->opt.smoother == 1, c->opt.krylov == 1,
-                     opt_omega(c->opt), c->opt.bottom_rtol, bottom_maxit(c)};
+                     opt_omega(c->opt), c->opt.bottom_rtol, bottom_maxit(c), c->inv_ready};
     const bool fp64 = sizeof(T) == 8;
     return launch_tail<T>(c->dim, c->L.back().g.nn > kTailWaveBottom,
                           c->tail_args + (fp64 ? 0 : kTailArgBytes),
@@ -933,6 +956,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
       break;
     }
     if (restart) {
+      HIP_TRY(prepare_inverse(c));
       SBM_TRY(run_cycle(c, nullptr, 1));
       if (rzf) {
         HIP_TRY(launch_finalize_sum(c->partials, nrz, c->scal + 4, c->st));
@@ -1052,6 +1076,7 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
       status = SBM_NOT_CONVERGED;
       break;
     }
+    HIP_TRY(prepare_inverse(c));
     s = run_cycle(c, f, keep_sweep ? 3 : cast ? 5 : (fused || keep ? 2 : 0));
     if (s != SBM_OK) return s;
   }
@@ -1160,6 +1185,7 @@ sbm_status sbm_set_options(sbm_ctx *c, const sbm_options *opts) {
   if (!same) {
     HIP_TRY(hipStreamSynchronize(c->st));
     drop_graphs(c);
+    c->inv_ready = false;
   }
   c->opt = *opts;
   return SBM_OK;
@@ -1336,12 +1362,13 @@ static sbm_status set_problem_impl(sbm_ctx *c, const double *psi_raw, int cube,
                            c->st));
   for (int l = 1; l < c->nlev; ++l) HIP_TRY(launch_coarsen_psi(c->L[l - 1], c->L[l], c->st));
   // tail level tables and the dense bottom matrix (needs the bottom psi)
+  c->inv_ready = false;
   if (c->tail64 >= 0)
-    HIP_TRY(tail_upload(c->L, 0, c->tail64, c->tail_args, c->tail_A, c->tail_lds_max,
-                        &c->tail_lds64, c->st));
+    HIP_TRY(tail_upload(c->L, 0, c->tail64, c->tail_args, c->tail_A, c->tail_inv, c->iflag + 13,
+                        c->tail_lds_max, &c->tail_lds64, c->st));
   if (c->tail32 >= 0)
-    HIP_TRY(tail_upload(c->L, 1, c->tail32, c->tail_args + kTailArgBytes, c->tail_A,
-                        c->tail_lds_max, &c->tail_lds32, c->st));
+    HIP_TRY(tail_upload(c->L, 1, c->tail32, c->tail_args + kTailArgBytes, c->tail_A, nullptr,
+                        nullptr, c->tail_lds_max, &c->tail_lds32, c->st));
   HIP_TRY(launch_rhs(L0, c->tr, b, L0.f, c->iflag, c->st));
   HIP_TRY(launch_check_diag(L0, c->iflag, c->st));
   int flags = 0;

@@ -49,6 +49,11 @@ struct TailArgs {
   int oA;
   const double *A;
   int fidx[kTailDenseLds];
+  // Inverse of the bottom operator over all n3 DOF (zero rows and columns on
+  // displacement DOF), its flag, and the parts a row is split into.
+  const double *inv;
+  const int *inv_bad;
+  int n3, parts;
 };
 static_assert(sizeof(TailArgs<double>) <= kTailArgBytes, "tail table too large");
 
@@ -379,9 +384,43 @@ struct Tail {
     __syncthreads();
   }
 
+  // X(B) = K_B^-1 F(B) with the inverse of tail_inverse: thread (part s, row i)
+  // sums its share of the row, the parts are added in order.  It takes the
+  // place of a CG of some n3 dependent iterations of 1 to 2 us (bound by
+  // latency).  Bound by reading n3^2 values from L2; the whole tail with a
+  // bottom of 112 nodes 259 -> 48 us, of 27 nodes 59 -> 45 us.
+  __device__ __forceinline__ void bottom_inverse(int *iters) const {
+    const int n3 = a.n3, pitch = (n3 + 63) & ~63;
+    const int s = threadIdx.x / pitch, i = threadIdx.x - s * pitch;
+    const int len = (n3 + a.parts - 1) / a.parts;
+    T *xb = (T *)(sm + a.oxb);
+    const T *fb_ = (const T *)(sm + a.ofb);
+    if (s < a.parts && i < n3) {
+      const int j1 = min(n3, (s + 1) * len);
+      double acc = 0.0;
+#pragma unroll 16
+      for (int j = s * len; j < j1; ++j) acc += a.inv[j * n3 + i] * fb_[j];
+      R()[s * n3 + i] = acc;
+    }
+    __syncthreads();
+    if (threadIdx.x < n3) {
+      double v = 0.0;
+      for (int q = 0; q < a.parts; ++q) v += R()[q * n3 + threadIdx.x];
+      xb[threadIdx.x] = v;
+    }
+    if (threadIdx.x == 0 && iters) *iters = 1;
+    __syncthreads();
+  }
+
   // X(B) = CG(K_B, F(B)) from zero, in FP64 in the first wave: Jacobi
   // preconditioning, stop at ||r|| <= rtol ||r0|| or maxit iterations.
   __device__ __forceinline__ void bottom(int *iters) const {
+    if constexpr (sizeof(T) == 8) {
+      if (o.inverse && *a.inv_bad == 0) {
+        bottom_inverse(iters);
+        return;
+      }
+    }
     if constexpr (WIDE) {
       bottom_wide(iters);
       return;
@@ -567,6 +606,47 @@ __global__ __launch_bounds__(64) void k_tail_assemble(const TailArgs<T> *__restr
   }
 }
 
+// Column b of the bottom's inverse: the bottom CG for the unit vector of DOF b,
+// a workgroup each (112 nodes: 336 columns side by side 247 us, one CG 215 us; 27
+// nodes 43 us).
+template <int DIM>
+__global__ __launch_bounds__(kTailThreads) void k_tail_inverse(
+    const TailArgs<double> *__restrict__ ap, double tol, int maxit) {
+  const TailArgs<double> &a = *ap;
+  extern __shared__ double smem[];
+  __shared__ double red[64];
+  const Geom g = a.gb;
+  const int n = (int)g.nn, id = threadIdx.x;
+  const int col = blockIdx.x, cc = col / n, cn = col - cc * n;
+  double *p = smem, *psi = smem + DIM * n;
+  for (int q = id; q < g.nc; q += blockDim.x) psi[q] = a.psib[q];
+  double *out = const_cast<double *>(a.inv) + (int64_t)col * a.n3;
+  BotRed R{red, 0};
+  double r[1][3] = {{0.0, 0.0, 0.0}}, d[1][3] = {{0.0, 0.0, 0.0}};
+  bool dir[1][3] = {{true, true, true}};
+  int cijk[1][3] = {{0, 0, 0}};
+  if (id < n) {
+    node_ijk(g, id, cijk[0][0], cijk[0][1], cijk[0][2]);
+    const uint32_t fb = face_bits(g, cijk[0][0], cijk[0][1], cijk[0][2]);
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+      dir[0][c] = ((g.dmask >> c) & fb) != 0u;
+      r[0][c] = !dir[0][c] && id == cn && c == cc ? 1.0 : 0.0;
+    }
+  }
+  __syncthreads();
+  // (a displacement DOF: zero load, zero column)
+  bot_cg<double, DIM, 1, false>(g, a.Cb, psi, p, r, d, dir, cijk, tol, maxit, R);
+  double rr = 0.0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) rr += r[0][c] * r[0][c];
+  rr = bot_allsum(rr, R);
+  if (id == 0 && !(rr <= tol * tol)) *const_cast<int *>(a.inv_bad) = 1;
+  if (id < n)
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) out[c * n + id] = d[0][c];
+}
+
 template <typename T>
 const T *tail_psi(const Level &L);
 template <>
@@ -643,6 +723,9 @@ size_t tail_layout(const std::vector<Level> &L, int l0, TailArgs<T> *a,
       t.nf = 0;  // no room in LDS: the stencil CG
   }
   t.A = dense_A;
+  t.n3 = d * (int)gb.nn;
+  t.parts = std::max(1, std::min(kTailThreads / ((t.n3 + 63) / 64 * 64),
+                                 (int)(d * L[l0].g.nn) / t.n3));
   if (a) *a = t;
   return off;
 }
@@ -660,7 +743,8 @@ int tail_level(const std::vector<Level> &L, int precision, size_t lds_max) {
 }
 
 hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void *dev,
-                       double *dense_A, size_t lds_max, size_t *lds_bytes, hipStream_t st) {
+                       double *dense_A, double *inv, int *inv_bad, size_t lds_max,
+                       size_t *lds_bytes, hipStream_t st) {
   hipError_t e;
   const int dim = L[0].g.dim;
   (void)hipGetLastError();
@@ -678,6 +762,8 @@ hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void 
     TailArgs<double> a{};
     *lds_bytes = tail_layout<double>(L, l0, &a, dense_A, lds_max);
     if (*lds_bytes == 0) return hipErrorInvalidValue;
+    a.inv = inv;
+    a.inv_bad = inv_bad;
     if ((e = hipMemcpyAsync(dev, &a, sizeof(a), hipMemcpyHostToDevice, st)) != hipSuccess) return e;
     if (a.nf > 0) {
       const TailArgs<double> *da = (const TailArgs<double> *)dev;
@@ -687,6 +773,18 @@ hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void 
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return hipStreamSynchronize(st);  // the table lives on this stack frame
+}
+
+hipError_t tail_inverse(const Level &B, const void *dev, double tol, int maxit, hipStream_t st) {
+  const int dim = B.g.dim, n = (int)B.g.nn;
+  if (dim * n > kTailInverse) return hipErrorInvalidValue;
+  const TailArgs<double> *a = (const TailArgs<double> *)dev;
+  const dim3 grid(dim * n), block((n + 63) / 64 * 64);
+  const size_t lds = sizeof(double) * (dim * n + B.g.nc);
+  (void)hipGetLastError();
+  if (dim == 3) hipLaunchKernelGGL(k_tail_inverse<3>, grid, block, lds, st, a, tol, maxit);
+  else hipLaunchKernelGGL(k_tail_inverse<2>, grid, block, lds, st, a, tol, maxit);
+  return hipGetLastError();
 }
 
 template <typename T>
