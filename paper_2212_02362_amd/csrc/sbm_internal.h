@@ -250,7 +250,8 @@ int grid_blocks(int64_t n);
 template <typename T>
 hipError_t launch_bottom_cg(const Level &L, const T *psi, const Coef<T> &C, const T *f, T *x,
                             T *r, T *p, T *Ap, double rtol, int maxit, int *iters,
-                            hipStream_t st);
+                            hipStream_t st,
+                            const int *inv_state = nullptr);
 // Bottom solve of the FP32 cycle: the FP64 CG on the FP32 load, the result
 // returned in FP32 (f64 / x64 / r / p / Ap: FP64 scratch of the bottom size).
 hipError_t launch_bottom_f32io(const Level &L, const float *f32, float *x32, double *f64,
@@ -269,23 +270,27 @@ constexpr int kTailMaxLevels = 6;
 constexpr size_t kTailArgBytes = 4096;
 constexpr size_t kTailDenseBytes = 64 * 64 * sizeof(double);
 constexpr int kTailWaveBottom = 64;  // bottoms up to this many nodes are solved in one wave
-// Bottoms of up to this many DOF (displacement DOF included) have their inverse
-// applied by the FP64 tail (see tail_inverse).
-constexpr int kTailInverse = 512;
+// Bottoms of up to kInverseNodes nodes have their inverse applied in FP64 cycles, in the
+// tail up to kTailInverse DOF (displacement DOF included; a row per thread).
+constexpr int kInverseNodes = 512, kTailInverse = 512;
 struct TailOpts {
   int nu_pre, nu_post, jacobi, reverse;
   double omega, rtol;
   int maxit;
-  int inverse;  // FP64: apply the inverse of tail_inverse (unless it flagged itself)
+  int inverse;  // FP64: apply the bottom's inverse where its state says it is there
 };
 int tail_level(const std::vector<Level> &L, int precision, size_t lds_max);
 hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void *dev,
-                       double *dense_A, double *inv, int *inv_bad, size_t lds_max,
-                       size_t *lds_bytes, hipStream_t st);
-// The inverse of the bottom operator (FP64 tail; inv of tail_upload, (DOF)^2), a
-// column per workgroup by the bottom CG to a relative residual of tol; *inv_bad (0
-// on entry) is set when a column misses it.
-hipError_t tail_inverse(const Level &B, const void *dev, double tol, int maxit, hipStream_t st);
+                       double *dense_A, const double *inv, const int *inv_state,
+                       size_t lds_max, size_t *lds_bytes, hipStream_t st);
+// The inverse of the bottom operator ((DOF)^2 values), a column per workgroup by
+// the bottom CG to a relative residual of tol; state (two ints, 0 on entry): [0]
+// is set when it is formed, [1] when a column misses tol.
+hipError_t launch_bottom_inverse(const Level &B, double *inv, int *state, double tol, int maxit,
+                                 hipStream_t st);
+// x = inv f, where the state says that inv is there.
+hipError_t launch_bottom_product(const Level &B, const double *inv, const int *state,
+                                 const double *f, double *x, hipStream_t st);
 template <typename T>
 hipError_t launch_tail(int dim, bool wide_bottom, const void *dev, size_t lds_bytes,
                        T *x, const T *f, const TailOpts &o, int *iters, hipStream_t st);
@@ -325,5 +330,7 @@ void set_coefs(Level &L, double lam, double mu, int dim);
 // One V-cycle of the uniform hierarchy of c from its finest level: x (in/out)
 // and f are finest-level vectors in FP64 (precision 0) or FP32 (precision 1).
 hipError_t base_vcycle(sbm_ctx *c, int precision, void *x, const void *f);
+// Forms what its FP64 cycles use besides the problem.
+hipError_t base_prepare(sbm_ctx *c);
 
 }  // namespace sbm

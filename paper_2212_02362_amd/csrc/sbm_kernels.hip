@@ -1126,8 +1126,10 @@ template <int DIM, int Q, typename IO>
 __global__ __launch_bounds__(kBotThreads) void k_bottom_lds64(Geom g, Coef<double> C,
                                                        const double *__restrict__ psi,
                                                        const IO *__restrict__ f, IO *x,
-                                                       double rtol, int maxit, int *iters) {
+                                                       double rtol, int maxit, int *iters,
+                                                       const int *inv_state) {
   extern __shared__ double smem[];
+  if (inv_state && inv_state[0] != 0 && inv_state[1] == 0) return;  // solved by the inverse
   __shared__ double red[64];
   BotRed R{red, 0};
   const int64_t n = g.nn;
@@ -1796,7 +1798,7 @@ static size_t bottom_lds64_bytes(const Geom &g) {
 template <typename T>
 hipError_t launch_bottom_cg(const Level &L, const T *psi, const Coef<T> &C, const T *f, T *x,
                             T *r, T *p, T *Ap, double rtol, int maxit, int *iters,
-                            hipStream_t st) {
+                            hipStream_t st, const int *inv_state) {
   if constexpr (sizeof(T) == 8) {
     const size_t by = bottom_lds64_bytes(L.g);
     if (bottom_fits_lds(L.g, by)) {
@@ -1806,17 +1808,17 @@ hipError_t launch_bottom_cg(const Level &L, const T *psi, const Coef<T> &C, cons
       if (L.g.dim == 3) {
         if (one)
           hipLaunchKernelGGL((k_bottom_lds64<3, 1, double>), dim3(1), dim3(nt), by, st, L.g, C, psi, f, x,
-                             rtol, maxit, iters);
+                             rtol, maxit, iters, inv_state);
         else
           hipLaunchKernelGGL((k_bottom_lds64<3, kBotQ, double>), dim3(1), dim3(nt), by, st, L.g, C, psi, f,
-                             x, rtol, maxit, iters);
+                             x, rtol, maxit, iters, inv_state);
       } else {
         if (one)
           hipLaunchKernelGGL((k_bottom_lds64<2, 1, double>), dim3(1), dim3(nt), by, st, L.g, C, psi, f, x,
-                             rtol, maxit, iters);
+                             rtol, maxit, iters, inv_state);
         else
           hipLaunchKernelGGL((k_bottom_lds64<2, kBotQ, double>), dim3(1), dim3(nt), by, st, L.g, C, psi, f,
-                             x, rtol, maxit, iters);
+                             x, rtol, maxit, iters, inv_state);
       }
       return hipGetLastError();
     }
@@ -1839,17 +1841,21 @@ hipError_t launch_bottom_f32io(const Level &L, const float *f32, float *x32, dou
     if (L.g.dim == 3) {
       if (one)
         hipLaunchKernelGGL((k_bottom_lds64<3, 1, float>), dim3(1), dim3(nt), by, st, L.g, L.c64,
-                           L.psi64, f32, x32, rtol, maxit, iters);
+                           L.psi64, f32, x32, rtol, maxit, iters,
+                           (const int *)nullptr);
       else
         hipLaunchKernelGGL((k_bottom_lds64<3, kBotQ, float>), dim3(1), dim3(nt), by, st, L.g,
-                           L.c64, L.psi64, f32, x32, rtol, maxit, iters);
+                           L.c64, L.psi64, f32, x32, rtol, maxit, iters,
+                           (const int *)nullptr);
     } else {
       if (one)
         hipLaunchKernelGGL((k_bottom_lds64<2, 1, float>), dim3(1), dim3(nt), by, st, L.g, L.c64,
-                           L.psi64, f32, x32, rtol, maxit, iters);
+                           L.psi64, f32, x32, rtol, maxit, iters,
+                           (const int *)nullptr);
       else
         hipLaunchKernelGGL((k_bottom_lds64<2, kBotQ, float>), dim3(1), dim3(nt), by, st, L.g,
-                           L.c64, L.psi64, f32, x32, rtol, maxit, iters);
+                           L.c64, L.psi64, f32, x32, rtol, maxit, iters,
+                           (const int *)nullptr);
     }
     return hipGetLastError();
   }
@@ -1919,7 +1925,8 @@ hipError_t launch_sensitivity(const Level &L, double lam, double mu, const Tract
   template hipError_t launch_from_split<T>(const Level &, const T *, T *, hipStream_t);         \
   template hipError_t launch_copy<T>(const T *, T *, int64_t, hipStream_t);                     \
   template hipError_t launch_bottom_cg<T>(const Level &, const T *, const Coef<T> &, const T *, \
-                                          T *, T *, T *, T *, double, int, int *, hipStream_t);
+                                          T *, T *, T *, T *, double, int, int *, hipStream_t, \
+                                          const int *);
 
 SBM_INST(double)
 SBM_INST(float)

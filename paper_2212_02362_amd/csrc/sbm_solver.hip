@@ -118,8 +118,9 @@ struct sbm_ctx {
   int tail64 = -1, tail32 = -1;
   char *tail_args = nullptr;
   double *tail_A = nullptr;  // dense bottom matrix of the tails
-  double *tail_inv = nullptr;  // inverse of the bottom operator (FP64 tail), flag in iflag[13]
-  bool inv_ready = false;      // it is that of the current problem and options
+  // inverse of the bottom operator (FP64 cycles), its state in iflag[13], [14]
+  double *tail_inv = nullptr;
+  bool inv_ready = false;  // formed for the current problem and options
   size_t tail_lds64 = 0, tail_lds32 = 0;
   size_t tail_lds_max = 64 * 1024;  // LDS bytes a workgroup may hold on this device
   // set while a cycle runs whose first finest-level half-sweep was already
@@ -314,7 +315,7 @@ static size_t carve(sbm_ctx *c, char *base) {
   c->b_r64 = cv.take<double>(nb);
   c->tail_args = cv.take<char>(2 * (int64_t)kTailArgBytes);
   c->tail_A = cv.take<double>((int64_t)(kTailDenseBytes / sizeof(double)));
-  c->tail_inv = cv.take<double>(nb <= kTailInverse ? nb * nb : 0);
+  c->tail_inv = cv.take<double>(B.g.nn <= kInverseNodes ? nb * nb : 0);
   return cv.off + 256;
 }
 
@@ -569,10 +570,16 @@ static void rz_set(sbm_ctx *c, const double *ss, bool fp64 = false) {
   c->rz_ss = on ? ss : nullptr;
 }
 
-static hipError_t bottom64(sbm_ctx *c, const double *f, double *x) {
+static bool inverse_ok(const sbm_ctx *c);
+// cycle: x is 0 on entry (the inverse may stand for the CG).
+static hipError_t bottom64(sbm_ctx *c, const double *f, double *x, bool cycle) {
   Level &B = c->L[c->nlev - 1];
+  const int *state = cycle && inverse_ok(c) ? c->iflag + 13 : nullptr;
+  hipError_t e;
+  if (state && (e = launch_bottom_product(B, c->tail_inv, state, f, x, c->st)) != hipSuccess)
+    return e;
   return launch_bottom_cg<double>(B, B.psi64, B.c64, f, x, c->b_r, c->b_p, c->b_Ap,
-                                  c->opt.bottom_rtol, bottom_maxit(c), c->iflag + 4, c->st);
+                                  c->opt.bottom_rtol, bottom_maxit(c), c->iflag + 4, c->st, state);
 }
 
 static hipError_t bottom32(sbm_ctx *c, const float *f, float *x) {
@@ -582,25 +589,34 @@ static hipError_t bottom32(sbm_ctx *c, const float *f, float *x) {
                              c->opt.bottom_rtol, bottom_maxit(c), c->iflag + 4, c->st);
 }
 
-// The bottom's inverse for the FP64 tail, once per problem before its first cycle:
-// as many CG solves as DOF side by side, where each cycle would make one (a 112-node
-// bottom: 247 us once against 215 us per cycle).  Where bottom_rtol is near its default 1e-12 and its iterations are not capped;
-// columns are solved to 1e-2 bottom_rtol, so a sum over 512 of them keeps
-// bottom_rtol.  A looser CG is cheaper and stays.
-static hipError_t prepare_inverse(sbm_ctx *c) {
+// Whether FP64 cycles may apply the bottom's inverse: the bottom is a coarse level
+// (its iterate starts from zero) of at most kInverseNodes nodes, bottom_rtol is
+// near its default 1e-12 and the iterations are not capped.  Its columns are
+// solved to 1e-2 bottom_rtol, so a sum over 1536 of them keeps bottom_rtol.  A
+// looser CG is cheaper and stays.
+static bool inverse_ok(const sbm_ctx *c) {
   const Level &B = c->L.back();
-  if (c->inv_ready || c->opt.precision != 0 || c->tail64 < 0 || c->opt.bottom_max_iter > 0 ||
-      !(c->opt.bottom_rtol >= 1e-13 && c->opt.bottom_rtol <= 1e-12) ||
-      c->dim * B.g.nn > kTailInverse)
-    return hipSuccess;
-  hipError_t e = launch_fill<int>(c->iflag + 13, 1, 0, c->st);
-  if (e != hipSuccess) return e;
-  if ((e = tail_inverse(B, c->tail_args, 1e-2 * c->opt.bottom_rtol, 2 * bottom_maxit(c),
-                        c->st)) != hipSuccess)
-    return e;
-  c->inv_ready = true;
-  return hipSuccess;
+  return c->nlev > 1 && B.g.nn <= kInverseNodes &&
+         (c->tail64 < 0 || c->dim * B.g.nn <= kTailInverse) && c->opt.bottom_max_iter <= 0 &&
+         c->opt.bottom_rtol >= 1e-13 && c->opt.bottom_rtol <= 1e-12;
 }
+
+// Forms the inverse once per problem, before cycle m (0 the first): as many CG
+// solves as DOF side by side, where each cycle would make one.  Up to 512 DOF they
+// take little more than one (112 nodes: 247 us against 215 us per cycle); larger
+// bottoms take a few (512 nodes: 1530 against 420 us), so theirs waits for a second
+// cycle (with it: 28^3 cells 9.7 -> 4.4 ms, 56x40x48 10.9 -> 5.2 ms).
+static hipError_t prepare_inverse(sbm_ctx *c, int m) {
+  const Level &B = c->L.back();
+  if (c->inv_ready || c->opt.precision != 0 || !inverse_ok(c) ||
+      (m < 1 && c->dim * B.g.nn > kTailInverse))
+    return hipSuccess;
+  c->inv_ready = true;
+  return launch_bottom_inverse(B, c->tail_inv, c->iflag + 13, 1e-2 * c->opt.bottom_rtol,
+                               2 * bottom_maxit(c), c->st);
+}
+
+hipError_t sbm::base_prepare(sbm_ctx *c) { return prepare_inverse(c, 1); }
 
 // V-cycle on level l: x (in/out), f (load), tmp (scratch of level l).
 template <typename T>
@@ -610,7 +626,7 @@ static hipError_t vcycle(sbm_ctx *c, int l, T *x, const T *f, T *tmp) {
     // the rest of the cycle in one workgroup (LDS-resident levels)
     ProfScope ps(c, SBM_PROF_BOTTOM, true);
     const TailOpts o{c->opt.nu_pre, c->opt.nu_post, c->opt.smoother == 1, c->opt.krylov == 1,
-                     opt_omega(c->opt), c->opt.bottom_rtol, bottom_maxit(c), c->inv_ready};
+                     opt_omega(c->opt), c->opt.bottom_rtol, bottom_maxit(c), inverse_ok(c)};
     const bool fp64 = sizeof(T) == 8;
     return launch_tail<T>(c->dim, c->L.back().g.nn > kTailWaveBottom,
                           c->tail_args + (fp64 ? 0 : kTailArgBytes),
@@ -618,7 +634,7 @@ static hipError_t vcycle(sbm_ctx *c, int l, T *x, const T *f, T *tmp) {
   }
   if (l == c->nlev - 1) {
     ProfScope ps(c, SBM_PROF_BOTTOM, true);
-    if constexpr (sizeof(T) == 8) return bottom64(c, f, x);
+    if constexpr (sizeof(T) == 8) return bottom64(c, f, x, true);
     else return bottom32(c, f, x);
   }
   Level &L = c->L[l];
@@ -956,7 +972,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
       break;
     }
     if (restart) {
-      HIP_TRY(prepare_inverse(c));
+      HIP_TRY(prepare_inverse(c, m));
       SBM_TRY(run_cycle(c, nullptr, 1));
       if (rzf) {
         HIP_TRY(launch_finalize_sum(c->partials, nrz, c->scal + 4, c->st));
@@ -1004,6 +1020,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
       continue;
     }
     if (hist && m < cap) hist[m] = rho;
+    HIP_TRY(prepare_inverse(c, m + 1));
     SBM_TRY(run_cycle(c, nullptr, castf ? 4 : 1));
     if (rzf) {
       HIP_TRY(launch_finalize_sum(c->partials, nrz, c->scal + 1, c->st));
@@ -1076,7 +1093,7 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
       status = SBM_NOT_CONVERGED;
       break;
     }
-    HIP_TRY(prepare_inverse(c));
+    HIP_TRY(prepare_inverse(c, m));
     s = run_cycle(c, f, keep_sweep ? 3 : cast ? 5 : (fused || keep ? 2 : 0));
     if (s != SBM_OK) return s;
   }
@@ -1186,6 +1203,7 @@ sbm_status sbm_set_options(sbm_ctx *c, const sbm_options *opts) {
     HIP_TRY(hipStreamSynchronize(c->st));
     drop_graphs(c);
     c->inv_ready = false;
+    HIP_TRY(launch_fill<int>(c->iflag + 13, 2, 0, c->st));
   }
   c->opt = *opts;
   return SBM_OK;
@@ -1734,7 +1752,7 @@ sbm_status sbm_bottom_solve(sbm_ctx *c, const double *f, double *x, int *iters) 
   NEED_PROBLEM(c);
   if (!f || !x) return fail(SBM_E_ARG, "NULL argument");
   NO_ALIAS(f, x);
-  HIP_TRY(bottom64(c, f, x));
+  HIP_TRY(bottom64(c, f, x, false));
   HIP_TRY(hipMemcpyAsync(c->host, c->iflag + 4, sizeof(int), hipMemcpyDeviceToHost, c->st));
   HIP_TRY(hipStreamSynchronize(c->st));
   if (iters) memcpy(iters, c->host, sizeof(int));

@@ -52,10 +52,36 @@ struct TailArgs {
   // Inverse of the bottom operator over all n3 DOF (zero rows and columns on
   // displacement DOF), its flag, and the parts a row is split into.
   const double *inv;
-  const int *inv_bad;
+  const int *inv_state;
   int n3, parts;
 };
 static_assert(sizeof(TailArgs<double>) <= kTailArgBytes, "tail table too large");
+
+// The state of the bottom's inverse: [0] it has been formed, [1] a column missed
+// its tolerance.
+__device__ __forceinline__ bool inverse_there(const int *state) {
+  return state[0] != 0 && state[1] == 0;
+}
+
+// Entries j0 .. j1 - 1 of row i of the inverse times f: 16 loads in flight at a time,
+// also in the last, shorter group.
+__device__ __forceinline__ double inverse_row(const double *__restrict__ inv, int n3, int i,
+                                              const double *f, int j0, int j1) {
+  double acc = 0.0;
+  for (int j = j0; j < j1; j += 16) {
+    double v[16], w[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int jc = min(j + q, j1 - 1);
+      v[q] = inv[(int64_t)jc * n3 + i];
+      w[q] = f[jc];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc += j + q < j1 ? v[q] * w[q] : 0.0;
+  }
+  return acc;
+}
 
 // Wave-scope ordering of LDS accesses between lanes of one wave (the bottom
 // CG runs in a single wave and needs no barrier).
@@ -396,11 +422,7 @@ struct Tail {
     T *xb = (T *)(sm + a.oxb);
     const T *fb_ = (const T *)(sm + a.ofb);
     if (s < a.parts && i < n3) {
-      const int j1 = min(n3, (s + 1) * len);
-      double acc = 0.0;
-#pragma unroll 16
-      for (int j = s * len; j < j1; ++j) acc += a.inv[j * n3 + i] * fb_[j];
-      R()[s * n3 + i] = acc;
+      R()[s * n3 + i] = inverse_row(a.inv, n3, i, fb_, s * len, min(n3, (s + 1) * len));
     }
     __syncthreads();
     if (threadIdx.x < n3) {
@@ -416,7 +438,7 @@ struct Tail {
   // preconditioning, stop at ||r|| <= rtol ||r0|| or maxit iterations.
   __device__ __forceinline__ void bottom(int *iters) const {
     if constexpr (sizeof(T) == 8) {
-      if (o.inverse && *a.inv_bad == 0) {
+      if (o.inverse && inverse_there(a.inv_state)) {
         bottom_inverse(iters);
         return;
       }
@@ -608,19 +630,18 @@ __global__ __launch_bounds__(64) void k_tail_assemble(const TailArgs<T> *__restr
 
 // Column b of the bottom's inverse: the bottom CG for the unit vector of DOF b,
 // a workgroup each (112 nodes: 336 columns side by side 247 us, one CG 215 us; 27
-// nodes 43 us).
+// nodes 43 us; 512 nodes: 1536 columns 1530 us, one CG 420 us).
 template <int DIM>
-__global__ __launch_bounds__(kTailThreads) void k_tail_inverse(
-    const TailArgs<double> *__restrict__ ap, double tol, int maxit) {
-  const TailArgs<double> &a = *ap;
+__global__ __launch_bounds__(kTailThreads) void k_bottom_inverse(
+    Geom g, Coef<double> C, const double *__restrict__ psib, double *__restrict__ inv,
+    int *__restrict__ state, double tol, int maxit) {
   extern __shared__ double smem[];
   __shared__ double red[64];
-  const Geom g = a.gb;
   const int n = (int)g.nn, id = threadIdx.x;
   const int col = blockIdx.x, cc = col / n, cn = col - cc * n;
   double *p = smem, *psi = smem + DIM * n;
-  for (int q = id; q < g.nc; q += blockDim.x) psi[q] = a.psib[q];
-  double *out = const_cast<double *>(a.inv) + (int64_t)col * a.n3;
+  for (int q = id; q < g.nc; q += blockDim.x) psi[q] = psib[q];
+  double *out = inv + (int64_t)col * (DIM * n);
   BotRed R{red, 0};
   double r[1][3] = {{0.0, 0.0, 0.0}}, d[1][3] = {{0.0, 0.0, 0.0}};
   bool dir[1][3] = {{true, true, true}};
@@ -636,15 +657,39 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_inverse(
   }
   __syncthreads();
   // (a displacement DOF: zero load, zero column)
-  bot_cg<double, DIM, 1, false>(g, a.Cb, psi, p, r, d, dir, cijk, tol, maxit, R);
+  bot_cg<double, DIM, 1, false>(g, C, psi, p, r, d, dir, cijk, tol, maxit, R);
   double rr = 0.0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) rr += r[0][c] * r[0][c];
   rr = bot_allsum(rr, R);
-  if (id == 0 && !(rr <= tol * tol)) *const_cast<int *>(a.inv_bad) = 1;
+  if (id == 0 && !(rr <= tol * tol)) state[1] = 1;
+  if (id == 0 && col == 0) state[0] = 1;
   if (id < n)
 #pragma unroll
     for (int c = 0; c < DIM; ++c) out[c * n + id] = d[0][c];
+}
+
+// x = inverse f for a bottom outside the tail (the tail holds two levels or more
+// in LDS): 64 rows per workgroup, a wave per sixteenth of their sums.  Without an
+// inverse it leaves x as it is and the CG launched behind it does the work.
+// Bound by the latency of n3 / 16 loads in flight 16 at a time (512 nodes: 22 us,
+// the CG 420 us).
+constexpr int kProdParts = 16;
+__global__ __launch_bounds__(64 * kProdParts) void k_bottom_product(
+    int n3, const double *__restrict__ inv, const int *__restrict__ state,
+    const double *__restrict__ f, double *__restrict__ x) {
+  __shared__ double part[kProdParts][64];
+  if (!inverse_there(state)) return;
+  const int lane = threadIdx.x & 63, s = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + lane, len = (n3 + kProdParts - 1) / kProdParts;
+  part[s][lane] = i < n3 ? inverse_row(inv, n3, i, f, s * len, min(n3, (s + 1) * len)) : 0.0;
+  __syncthreads();
+  if (s == 0 && i < n3) {
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < kProdParts; ++q) v += part[q][lane];
+    x[i] = v;
+  }
 }
 
 template <typename T>
@@ -743,8 +788,8 @@ int tail_level(const std::vector<Level> &L, int precision, size_t lds_max) {
 }
 
 hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void *dev,
-                       double *dense_A, double *inv, int *inv_bad, size_t lds_max,
-                       size_t *lds_bytes, hipStream_t st) {
+                       double *dense_A, const double *inv, const int *inv_state,
+                       size_t lds_max, size_t *lds_bytes, hipStream_t st) {
   hipError_t e;
   const int dim = L[0].g.dim;
   (void)hipGetLastError();
@@ -763,7 +808,7 @@ hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void 
     *lds_bytes = tail_layout<double>(L, l0, &a, dense_A, lds_max);
     if (*lds_bytes == 0) return hipErrorInvalidValue;
     a.inv = inv;
-    a.inv_bad = inv_bad;
+    a.inv_state = inv_state;
     if ((e = hipMemcpyAsync(dev, &a, sizeof(a), hipMemcpyHostToDevice, st)) != hipSuccess) return e;
     if (a.nf > 0) {
       const TailArgs<double> *da = (const TailArgs<double> *)dev;
@@ -775,15 +820,28 @@ hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void 
   return hipStreamSynchronize(st);  // the table lives on this stack frame
 }
 
-hipError_t tail_inverse(const Level &B, const void *dev, double tol, int maxit, hipStream_t st) {
+hipError_t launch_bottom_inverse(const Level &B, double *inv, int *state, double tol, int maxit,
+                                 hipStream_t st) {
   const int dim = B.g.dim, n = (int)B.g.nn;
-  if (dim * n > kTailInverse) return hipErrorInvalidValue;
-  const TailArgs<double> *a = (const TailArgs<double> *)dev;
+  if (n > kTailThreads) return hipErrorInvalidValue;
   const dim3 grid(dim * n), block((n + 63) / 64 * 64);
   const size_t lds = sizeof(double) * (dim * n + B.g.nc);
   (void)hipGetLastError();
-  if (dim == 3) hipLaunchKernelGGL(k_tail_inverse<3>, grid, block, lds, st, a, tol, maxit);
-  else hipLaunchKernelGGL(k_tail_inverse<2>, grid, block, lds, st, a, tol, maxit);
+  if (dim == 3)
+    hipLaunchKernelGGL(k_bottom_inverse<3>, grid, block, lds, st, B.g, B.c64, B.psi64, inv, state,
+                       tol, maxit);
+  else
+    hipLaunchKernelGGL(k_bottom_inverse<2>, grid, block, lds, st, B.g, B.c64, B.psi64, inv, state,
+                       tol, maxit);
+  return hipGetLastError();
+}
+
+hipError_t launch_bottom_product(const Level &B, const double *inv, const int *state,
+                                 const double *f, double *x, hipStream_t st) {
+  const int n3 = B.g.dim * (int)B.g.nn;
+  (void)hipGetLastError();
+  hipLaunchKernelGGL(k_bottom_product, dim3((n3 + 63) / 64), dim3(64 * kProdParts), 0, st, n3, inv,
+                     state, f, x);
   return hipGetLastError();
 }
 
