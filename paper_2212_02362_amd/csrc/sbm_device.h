@@ -207,6 +207,46 @@ __device__ __forceinline__ void stencil3(const CO &C, const T (&P)[2][2][2], UF 
   }
 }
 
+// 2D eq. K at one node, as stencil3: P[c1][c0] is the psi of cell (i-1+c0, j-1+c1)
+// and U(c, dx, dy) the c-th displacement at the neighbour (i+dx, j+dy).
+template <typename T, typename CO, typename UF>
+__device__ __forceinline__ void stencil2(const CO &C, const T (&P)[2][2], UF &&U, T out[3],
+                                         T diag[3]) {
+      T E[2][2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        E[0][s] = P[0][s] + P[1][s];
+        E[1][s] = P[s][0] + P[s][1];
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const T uc = U(c, 0, 0);
+        const T xp = U(c, 1, 0) - uc, xm = U(c, -1, 0) - uc;
+        const T yp = U(c, 0, 1) - uc, ym = U(c, 0, -1) - uc;
+        out[c] = -(coef_cd(C, c, 0) * (E[0][1] * xp + E[0][0] * xm) +
+                   coef_cd(C, c, 1) * (E[1][1] * yp + E[1][0] * ym));
+        diag[c] = coef_cd(C, c, 0) * (E[0][0] + E[0][1]) + coef_cd(C, c, 1) * (E[1][0] + E[1][1]);
+      }
+      const T cp = coef_cp(C, 0), cm = coef_cm(C, 0);
+      const T ux0 = U(0, 0, 0), uy0 = U(1, 0, 0);
+      T rx = T(0), ry = T(0);
+#pragma unroll
+      for (int qa = 0; qa < 2; ++qa)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+          const int sa = 2 * qa - 1, sb = 2 * qb - 1;
+          const T F = P[qb][qa];
+          const T w = (sa * sb > 0) ? F : -F;
+          const T uxab = U(0, sa, sb), uyab = U(1, sa, sb);
+          const T uxa = U(0, sa, 0), uxb = U(0, 0, sb);
+          const T uya = U(1, sa, 0), uyb = U(1, 0, sb);
+          rx += w * (cp * (uyab - uy0) + cm * (uyb - uya));
+          ry += w * (cp * (uxab - ux0) + cm * (uxa - uxb));
+        }
+      out[0] -= rx;
+      out[1] -= ry;
+}
+
 // Evaluates (K u)(n) for all components and the diagonal at node (i, j, k).
 // Neighbour offsets are clamped at the box boundary: every term that would
 // reach outside carries a zero psi weight, so the clamped value never counts.
@@ -326,45 +366,13 @@ __device__ __forceinline__ void node_stencil(const G &g, const CO &C,
     T P[2][2];  // P[oy][ox]
 #pragma unroll
     for (int q = 0; q < 4; ++q) P[q >> 1][q & 1] = pin[q >> 1][q & 1] ? pv[q >> 1][q & 1] : T(0);
-    T E[2][2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      E[0][s] = P[0][s] + P[1][s];
-      E[1][s] = P[s][0] + P[s][1];
-    }
     auto U = [&](int c, int dx, int dy) -> T { return V[c][(dx + 1) + 3 * (dy + 1)]; };
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const T uc = U(c, 0, 0);
-      const T xp = U(c, 1, 0) - uc, xm = U(c, -1, 0) - uc;
-      const T yp = U(c, 0, 1) - uc, ym = U(c, 0, -1) - uc;
-      out[c] = -(coef_cd(C, c, 0) * (E[0][1] * xp + E[0][0] * xm) +
-                 coef_cd(C, c, 1) * (E[1][1] * yp + E[1][0] * ym));
-      diag[c] = coef_cd(C, c, 0) * (E[0][0] + E[0][1]) + coef_cd(C, c, 1) * (E[1][0] + E[1][1]);
-    }
-    const T cp = coef_cp(C, 0), cm = coef_cm(C, 0);
-    const T ux0 = U(0, 0, 0), uy0 = U(1, 0, 0);
-    T rx = T(0), ry = T(0);
-#pragma unroll
-    for (int qa = 0; qa < 2; ++qa)
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
-        const int sa = 2 * qa - 1, sb = 2 * qb - 1;
-        const T F = P[qb][qa];
-        const T w = (sa * sb > 0) ? F : -F;
-        const T uxab = U(0, sa, sb), uyab = U(1, sa, sb);
-        const T uxa = U(0, sa, 0), uxb = U(0, 0, sb);
-        const T uya = U(1, sa, 0), uyb = U(1, 0, sb);
-        rx += w * (cp * (uyab - uy0) + cm * (uyb - uya));
-        ry += w * (cp * (uxab - ux0) + cm * (uxa - uxb));
-      }
-    out[0] -= rx;
-    out[1] -= ry;
+    stencil2<T>(C, P, U, out, diag);
     out[2] = T(0);
     diag[2] = T(0);
     if (ctr) {
-      ctr[0] = ux0;
-      ctr[1] = uy0;
+      ctr[0] = U(0, 0, 0);
+      ctr[1] = U(1, 0, 0);
       ctr[2] = T(0);
     }
   }

@@ -283,6 +283,16 @@ int tail_level(const std::vector<Level> &L, int precision, size_t lds_max);
 hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void *dev,
                        double *dense_A, const double *inv, const int *inv_state,
                        size_t lds_max, size_t *lds_bytes, hipStream_t st);
+// The legs of a 2D FP64 V-cycle on level L over Lc (sbm_leg2d.hip), nu 1 or 2
+// sweeps, xout another buffer than xin.  Down: xout = xin (NULL: zero) smoothed from
+// first_colour, fc = the restricted residual, ec (nullable) = 0.  Up: xout = xin +
+// the prolongation of e, smoothed.
+hipError_t launch_leg2_down(const Level &L, const Level &Lc, const double *xin, const double *f,
+                            double *xout, double *fc, double *ec, double omega, int first_colour,
+                            int nu, hipStream_t st);
+hipError_t launch_leg2_up(const Level &L, const Level &Lc, const double *xin, const double *f,
+                          double *xout, const double *e, double omega, int first_colour, int nu,
+                          hipStream_t st);
 // The inverse of the bottom operator ((DOF)^2 values), a column per workgroup by
 // the bottom CG to a relative residual of tol; state (two ints, 0 on entry): [0]
 // is set when it is formed, [1] when a column misses tol.

@@ -618,6 +618,16 @@ static hipError_t prepare_inverse(sbm_ctx *c, int m) {
 
 hipError_t sbm::base_prepare(sbm_ctx *c) { return prepare_inverse(c, 1); }
 
+// Whether level l runs its legs of a FP64 V-cycle in one launch each: 2D, one or two
+// sweeps on either leg (the halo of more would outgrow the tile), above the tail,
+// whose levels need no launches.
+static bool leg2_ok(const sbm_ctx *c, int l) {
+  return c->dim == 2 && c->opt.precision == 0 && c->opt.smoother == 0 &&
+         c->opt.fused_sweep == 0 && c->opt.nu_pre >= 1 && c->opt.nu_pre <= 2 &&
+         c->opt.nu_post >= 1 && c->opt.nu_post <= 2 && l < c->nlev - 1 &&
+         (c->tail64 < 0 || l < c->tail64);
+}
+
 // V-cycle on level l: x (in/out), f (load), tmp (scratch of level l).
 template <typename T>
 static hipError_t vcycle(sbm_ctx *c, int l, T *x, const T *f, T *tmp) {
@@ -639,6 +649,23 @@ static hipError_t vcycle(sbm_ctx *c, int l, T *x, const T *f, T *tmp) {
   }
   Level &L = c->L[l];
   Level &C = c->L[l + 1];
+  if constexpr (sizeof(T) == 8) {
+    if (leg2_ok(c, l)) {
+      const double om = opt_omega(c->opt);
+      const bool zero = l > 0 || c->zero_start;
+      if (l == 0) c->zero_start = false;
+      {
+        ProfScope ps(c, SBM_PROF_SMOOTH, l == 0);
+        if ((e = launch_leg2_down(L, C, zero ? nullptr : x, f, tmp, C.f,
+                                  leg2_ok(c, l + 1) ? nullptr : C.e, om, 0, c->opt.nu_pre,
+                                  c->st)) != hipSuccess)
+          return e;
+      }
+      if ((e = vcycle<double>(c, l + 1, C.e, C.f, C.t)) != hipSuccess) return e;
+      ProfScope ps(c, SBM_PROF_SMOOTH, l == 0);
+      return launch_leg2_up(L, C, tmp, f, x, C.e, om, c->opt.krylov == 1, c->opt.nu_post, c->st);
+    }
+  }
   if ((e = smooth<T>(c, l, x, f, tmp, c->opt.nu_pre, false, true)) != hipSuccess) return e;
   {
     ProfScope ps(c, SBM_PROF_RESIDUAL, l == 0);
@@ -785,7 +812,7 @@ static hipError_t cycle_body(sbm_ctx *c, const double *f, int mode) {
       // and scale it themselves (the FP64 z is never written)
       return launch_store_sqrt(c->scal, c->scal + 6, c->st);
     }
-    if (L0.g.hx && skip && c->tail64 != 0) {
+    if ((L0.g.hx && skip && c->tail64 != 0) || leg2_ok(c, 0)) {
       c->zero_start = true;
     } else if (skip && c->tail64 != 0) {
       if ((e = launch_zero_sweep<double>(L0, L0.psi64, L0.c64, c->kr, L0.t, opt_omega(c->opt), 0,
@@ -1055,7 +1082,8 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
   // makes the next cycle's first half-sweep (the iterate itself is left as it is, so a
   // converged solve returns the tested iterate)
   const bool fused = c->opt.precision == 0 && c->opt.smoother == 0 && c->opt.nu_pre >= 1 &&
-                     c->nlev > 1 && c->tail64 != 0 && (L0.g.hx != 0 || residual_sweep_ok(L0));
+                     c->nlev > 1 && c->tail64 != 0 && (L0.g.hx != 0 || residual_sweep_ok(L0)) &&
+                     !leg2_ok(c, 0);
   // mixed: the convergence test keeps f - K x0 for the cycle's cast, which
   // also makes the FP32 cycle's first half-sweep when the finest level
   // smooths outside the tail
