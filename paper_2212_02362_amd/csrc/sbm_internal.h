@@ -208,6 +208,15 @@ hipError_t launch_rhs(const Level &L, const Traction &tr, const double *b, doubl
                       hipStream_t st);
 hipError_t launch_check_diag(const Level &L, int *flag, hipStream_t st);
 hipError_t launch_finalize_sum(const double *partials, int n, double *out, hipStream_t st);
+// The same for one or two (b nullable) arrays of n partials, the sums also written
+// to pinned host memory, each followed by the ticket.
+struct HostSum {
+  const double *partials;
+  double *out, *host;
+  unsigned long long *ticket;
+};
+hipError_t launch_finalize_host(const HostSum &a, const HostSum *b, int n,
+                                unsigned long long ticket, hipStream_t st);
 hipError_t launch_dot_free(const Level &L, const double *a, const ZSrc &b, double *partials,
                            hipStream_t st);
 // *s_out = sqrt(*ss) (the scale of the mixed preconditioner's output).

@@ -730,9 +730,8 @@ __global__ __launch_bounds__(kBlock) void k_check_diag(Geom g, const double *__r
 
 // ------------------------------------------------------------ reductions --
 
-// Deterministic sum of n partials by one block of 1024 threads.
-__global__ __launch_bounds__(1024) void k_finalize_sum(const double *__restrict__ partials, int n,
-                                                       double *__restrict__ out) {
+// Deterministic sum of n partials by one block of 1024 threads (in thread 0).
+__device__ __forceinline__ double sum_partials(const double *__restrict__ partials, int n) {
   __shared__ double lds[1024 / 64 + 1];
   double s = 0.0;
   int q = threadIdx.x;
@@ -750,10 +749,28 @@ __global__ __launch_bounds__(1024) void k_finalize_sum(const double *__restrict_
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
   if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
+  double t = 0.0;
+  if (threadIdx.x == 0)
     for (int w = 0; w < 16; ++w) t += lds[w];
-    *out = t;
+  return t;
+}
+
+__global__ __launch_bounds__(1024) void k_finalize_sum(const double *__restrict__ partials, int n,
+                                                       double *__restrict__ out) {
+  const double t = sum_partials(partials, n);
+  if (threadIdx.x == 0) *out = t;
+}
+
+// The sums of one or two arrays of partials (a block each), also into pinned host
+// memory: the value, then its ticket, which the host waits for (see wait_host).
+__global__ __launch_bounds__(1024) void k_finalize_host(HostSum a, HostSum b, int n,
+                                                        unsigned long long ticket) {
+  const HostSum h = blockIdx.x == 0 ? a : b;
+  const double t = sum_partials(h.partials, n);
+  if (threadIdx.x == 0) {
+    *h.out = t;
+    __hip_atomic_store(h.host, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(h.ticket, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -1635,6 +1652,11 @@ hipError_t launch_from_split(const Level &L, const T *src, T *dst, hipStream_t s
 hipError_t launch_check_diag(const Level &L, int *flag, hipStream_t st) {
   if (L.g.dim == 3) SBM_LAUNCH((k_check_diag<3>), num_blocks(L.g.nn), kBlock, st, L.g, L.psi64, flag);
   SBM_LAUNCH((k_check_diag<2>), num_blocks(L.g.nn), kBlock, st, L.g, L.psi64, flag);
+}
+
+hipError_t launch_finalize_host(const HostSum &a, const HostSum *b, int n,
+                                unsigned long long ticket, hipStream_t st) {
+  SBM_LAUNCH(k_finalize_host, b ? 2 : 1, 1024, st, a, b ? *b : a, n, ticket);
 }
 
 hipError_t launch_finalize_sum(const double *partials, int n, double *out, hipStream_t st) {

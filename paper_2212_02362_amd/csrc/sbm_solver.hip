@@ -12,6 +12,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <initializer_list>
 #include <mutex>
 #include <string>
@@ -66,7 +67,8 @@ struct sbm_ctx {
   int *iflag = nullptr;    // device int flags / counters
   // bottom scratch
   double *b_r = nullptr, *b_p = nullptr, *b_Ap = nullptr, *b_x64 = nullptr, *b_r64 = nullptr;
-  double *host = nullptr;  // pinned host scalars
+  double *host = nullptr;  // pinned host scalars: 32 values, then their tickets
+  unsigned long long ticket = 0;  // of the latest sum the host waits for
   bool have_problem = false;
   sbm_material mat{};
   sbm_bc bc{};
@@ -694,6 +696,36 @@ hipError_t sbm::base_vcycle(sbm_ctx *c, int precision, void *x, const void *f) {
   return vcycle<double>(c, 0, (double *)x, (const double *)f, L0.t);
 }
 
+// Sums that the host decides on go straight to pinned memory (slot s of c->host, its
+// ticket 32 slots on), where it waits for them: a copy and a synchronisation of the
+// stream took some 10 us more per sum, of cycles of 80 to 200 us on small grids.
+static HostSum host_sum(sbm_ctx *c, const double *partials, int slot) {
+  return HostSum{partials, c->scal + slot, c->host + slot,
+                 (unsigned long long *)(c->host + 32 + slot)};
+}
+
+// Waits for the ticket of a slot.  Past 50 ms, and where live timing reads events, the
+// stream is synchronised, which also reports its errors.
+static sbm_status wait_host(sbm_ctx *c, int slot) {
+  const unsigned long long *t = (const unsigned long long *)(c->host + 32 + slot);
+  const auto t0 = std::chrono::steady_clock::now();
+  bool there = false;
+  for (int spin = 0; !there && !c->prof_on; ++spin) {
+    there = __atomic_load_n(t, __ATOMIC_ACQUIRE) == c->ticket;
+    if ((spin & 1023) == 1023 &&
+        std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50))
+      break;
+  }
+  if (!there) HIP_TRY(hipStreamSynchronize(c->st));
+  if (c->prof_on) prof_harvest(c);
+  return SBM_OK;
+}
+
+static sbm_status sum_to_host(sbm_ctx *c, const double *partials, int n, int slot) {
+  HIP_TRY(launch_finalize_host(host_sum(c, partials, slot), nullptr, n, ++c->ticket, c->st));
+  return wait_host(c, slot);
+}
+
 // ||r||_2^2 of the level-0 residual f - K u (free DOF), synchronising.
 static sbm_status residual_norm2(sbm_ctx *c, const double *u, const double *f, double *out) {
   Level &L = c->L[0];
@@ -701,10 +733,8 @@ static sbm_status residual_norm2(sbm_ctx *c, const double *u, const double *f, d
     ProfScope ps(c, SBM_PROF_NORM, true);
     HIP_TRY((launch_residual<double>(L, L.psi64, L.c64, u, f, nullptr, c->partials, c->st)));
   }
-  HIP_TRY(launch_finalize_sum(c->partials, stencil_partials(L), c->scal, c->st));
-  HIP_TRY(hipMemcpyAsync(c->host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->st));
-  HIP_TRY(hipStreamSynchronize(c->st));
-  if (c->prof_on) prof_harvest(c);
+  sbm_status s = sum_to_host(c, c->partials, stencil_partials(L), 0);
+  if (s != SBM_OK) return s;
   *out = c->host[0];
   return SBM_OK;
 }
@@ -718,10 +748,8 @@ static sbm_status residual_norm2_sweep(sbm_ctx *c, const double *u, const double
     ProfScope ps(c, SBM_PROF_NORM, true);
     HIP_TRY(launch_residual_sweep(L, u, f, L.t, opt_omega(c->opt), 0, c->partials, c->st));
   }
-  HIP_TRY(launch_finalize_sum(c->partials, stencil_partials(L), c->scal, c->st));
-  HIP_TRY(hipMemcpyAsync(c->host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->st));
-  HIP_TRY(hipStreamSynchronize(c->st));
-  if (c->prof_on) prof_harvest(c);
+  sbm_status s = sum_to_host(c, c->partials, stencil_partials(L), 0);
+  if (s != SBM_OK) return s;
   *out = c->host[0];
   return SBM_OK;
 }
@@ -735,10 +763,8 @@ static sbm_status residual_norm2_keep(sbm_ctx *c, const double *u, const double 
     ProfScope ps(c, SBM_PROF_NORM, true);
     HIP_TRY((launch_residual<double>(L, L.psi64, L.c64, u, f, L.t, c->partials, c->st)));
   }
-  HIP_TRY(launch_finalize_sum(c->partials, stencil_partials(L), c->scal, c->st));
-  HIP_TRY(hipMemcpyAsync(c->host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->st));
-  HIP_TRY(hipStreamSynchronize(c->st));
-  if (c->prof_on) prof_harvest(c);
+  sbm_status s = sum_to_host(c, c->partials, stencil_partials(L), 0);
+  if (s != SBM_OK) return s;
   *out = c->host[0];
   return SBM_OK;
 }
@@ -754,10 +780,8 @@ static sbm_status residual_norm2_cast(sbm_ctx *c, const double *u, const double 
     ProfScope ps(c, SBM_PROF_NORM, true);
     HIP_TRY(launch_residual_cast(L, u, f, L.f32, c->scal + 8, c->partials, c->st));
   }
-  HIP_TRY(launch_finalize_sum(c->partials, stencil_partials(L), c->scal, c->st));
-  HIP_TRY(hipMemcpyAsync(c->host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->st));
-  HIP_TRY(hipStreamSynchronize(c->st));
-  if (c->prof_on) prof_harvest(c);
+  sbm_status s = sum_to_host(c, c->partials, stencil_partials(L), 0);
+  if (s != SBM_OK) return s;
   *out = c->host[0];
   return SBM_OK;
 }
@@ -931,14 +955,6 @@ static sbm_status run_cycle(sbm_ctx *c, const double *f, int mode) {
   return SBM_OK;
 }
 
-// Finalises `n` partials into scal[slot] and copies scal[slot] to host[slot].
-static sbm_status fin_to_host(sbm_ctx *c, const double *partials, int n, int slot) {
-  HIP_TRY(launch_finalize_sum(partials, n, c->scal + slot, c->st));
-  HIP_TRY(hipMemcpyAsync(c->host + slot, c->scal + slot, sizeof(double), hipMemcpyDeviceToHost,
-                         c->st));
-  return SBM_OK;
-}
-
 #define SBM_TRY(expr)                      \
   do {                                     \
     sbm_status s_ = (expr);                \
@@ -947,8 +963,8 @@ static sbm_status fin_to_host(sbm_ctx *c, const double *partials, int n, int slo
 
 // Flexible CG (Polak-Ribiere beta) on the finest level, preconditioned by one
 // V-cycle from zero per iteration.  Device scalars: scal[0] = r.r,
-// scal[1] = r.z (new), scal[2] = p.q, scal[3] = r.z (old z), scal[4] = r.z
-// of the previous iteration, scal[5] = alpha of the last update; mixed:
+// scal[next] = r.z (new), scal[2] = p.q, scal[3] = r.z (old z), scal[prev] = r.z
+// of the previous iteration (slots 1 and 4 in turn), scal[5] = alpha of the last update; mixed:
 // scal[6] = the scale s of z = s e32, scal[7] = s^2 of the cast the CG update
 // makes.  The update
 // x += alpha p is deferred to the pass that forms the next direction (which
@@ -973,12 +989,11 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
     ProfScope ps(c, SBM_PROF_NORM, true);
     HIP_TRY((launch_residual<double>(L0, L0.psi64, L0.c64, c->x0, f, c->kr, c->partials, c->st)));
   }
-  SBM_TRY(fin_to_host(c, c->partials, ns, 0));
-  HIP_TRY(hipStreamSynchronize(c->st));
+  SBM_TRY(sum_to_host(c, c->partials, ns, 0));
   rho = fnorm > 0.0 ? sqrt(c->host[0]) / fnorm : (c->host[0] > 0.0 ? INFINITY : 0.0);
   if (hist && cap > 0) hist[0] = rho;
   bool restart = true;
-  int m = 0;
+  int m = 0, next = 1, prev = 4;
   for (;;) {
     if (!isfinite(rho)) {
       status = fail(SBM_E_NONFINITE, "non-finite residual at iteration " + std::to_string(m));
@@ -1002,33 +1017,33 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
       HIP_TRY(prepare_inverse(c, m));
       SBM_TRY(run_cycle(c, nullptr, 1));
       if (rzf) {
-        HIP_TRY(launch_finalize_sum(c->partials, nrz, c->scal + 4, c->st));
+        HIP_TRY(launch_finalize_sum(c->partials, nrz, c->scal + prev, c->st));
       } else {
         HIP_TRY(launch_dot_free(L0, c->kr, z, c->partials, c->st));
-        HIP_TRY(launch_finalize_sum(c->partials, nb, c->scal + 4, c->st));
+        HIP_TRY(launch_finalize_sum(c->partials, nb, c->scal + prev, c->st));
       }
       HIP_TRY(launch_xpby_x(L0, c->x0, c->kp, z, nullptr, nullptr, nullptr, nullptr, c->st));
       restart = false;
     }
     HIP_TRY(launch_apply_dot(L0, c->kp, c->kq, c->partials, c->st));
-    SBM_TRY(fin_to_host(c, c->partials, ns, 2));
-    HIP_TRY(hipStreamSynchronize(c->st));
-    if (c->prof_on) prof_harvest(c);
-    if (!(c->host[2] > 0.0)) {
-      status = fail(SBM_E_DIVERGED, "preconditioned CG lost positivity (p.Kp <= 0)");
-      break;
-    }
+    // p.Kp is checked with r.r below, in one wait: until then only kr, kq and alpha
+    // depend on it, and they are not read after a failure
+    HIP_TRY(launch_finalize_host(host_sum(c, c->partials, 2), nullptr, ns, ++c->ticket, c->st));
     // r -= alpha q; the iterate update x += alpha p (alpha kept in scal[5]) is
     // made by the next direction update, or below when the iteration ends.
     // Mixed: the same pass casts r / s for the next cycle, s = the norm of
     // the residual before the update (scal[0] -> scal[7]).
     if (castf) HIP_TRY(launch_copy<double>(c->scal, c->scal + 7, 1, c->st));
-    HIP_TRY(launch_cg_update_r(L0, c->kr, c->kq, z, c->scal + 4, c->scal + 2, c->scal + 5,
+    HIP_TRY(launch_cg_update_r(L0, c->kr, c->kq, z, c->scal + prev, c->scal + 2, c->scal + 5,
                                c->partials, c->partials2, c->st, castf ? L0.f32 : nullptr,
                                castf ? c->scal + 7 : nullptr));
-    SBM_TRY(fin_to_host(c, c->partials, nb, 0));
-    SBM_TRY(fin_to_host(c, c->partials2, nb, 3));
-    HIP_TRY(hipStreamSynchronize(c->st));
+    const HostSum rz_old = host_sum(c, c->partials2, 3);
+    HIP_TRY(launch_finalize_host(host_sum(c, c->partials, 0), &rz_old, nb, ++c->ticket, c->st));
+    SBM_TRY(wait_host(c, 0));  // and slot 2, written by the launch before
+    if (!(c->host[2] > 0.0)) {
+      status = fail(SBM_E_DIVERGED, "preconditioned CG lost positivity (p.Kp <= 0)");
+      break;
+    }
     ++m;
     rho = fnorm > 0.0 ? sqrt(c->host[0]) / fnorm : 0.0;
     if (rho <= c->opt.rtol) {
@@ -1039,8 +1054,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
         HIP_TRY((launch_residual<double>(L0, L0.psi64, L0.c64, c->x0, f, c->kr, c->partials,
                                          c->st)));
       }
-      SBM_TRY(fin_to_host(c, c->partials, ns, 0));
-      HIP_TRY(hipStreamSynchronize(c->st));
+      SBM_TRY(sum_to_host(c, c->partials, ns, 0));
       rho = fnorm > 0.0 ? sqrt(c->host[0]) / fnorm : 0.0;
       if (hist && m < cap) hist[m] = rho;
       if (rho > c->opt.rtol) restart = true;
@@ -1050,14 +1064,14 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
     HIP_TRY(prepare_inverse(c, m + 1));
     SBM_TRY(run_cycle(c, nullptr, castf ? 4 : 1));
     if (rzf) {
-      HIP_TRY(launch_finalize_sum(c->partials, nrz, c->scal + 1, c->st));
+      HIP_TRY(launch_finalize_sum(c->partials, nrz, c->scal + next, c->st));
     } else {
       HIP_TRY(launch_dot_free(L0, c->kr, z, c->partials, c->st));
-      HIP_TRY(launch_finalize_sum(c->partials, nb, c->scal + 1, c->st));
+      HIP_TRY(launch_finalize_sum(c->partials, nb, c->scal + next, c->st));
     }
-    HIP_TRY(launch_xpby_x(L0, c->x0, c->kp, z, c->scal + 1, c->scal + 3, c->scal + 4,
+    HIP_TRY(launch_xpby_x(L0, c->x0, c->kp, z, c->scal + next, c->scal + 3, c->scal + prev,
                           c->scal + 5, c->st));
-    HIP_TRY(launch_copy<double>(c->scal + 1, c->scal + 4, 1, c->st));
+    std::swap(next, prev);
   }
   if (ncyc) *ncyc = m;
   if (final_rel) *final_rel = rho;
@@ -1210,11 +1224,12 @@ sbm_status sbm_create(const sbm_grid *grid, const sbm_options *opts, void *works
     c->tail64 = tail_level(c->L, 0, (size_t)lds);
     c->tail32 = tail_level(c->L, 1, (size_t)lds);
   }
-  hipError_t e = hipHostMalloc((void **)&c->host, 64 * sizeof(double), hipHostMallocDefault);
+  hipError_t e = hipHostMalloc((void **)&c->host, 64 * sizeof(double), hipHostMallocCoherent);
   if (e != hipSuccess) {
     delete c;
     return fail(SBM_E_HIP, std::string("hipHostMalloc: ") + hipGetErrorString(e));
   }
+  memset(c->host, 0, 64 * sizeof(double));
   *out = c;
   return SBM_OK;
 }
