@@ -50,6 +50,14 @@ ALGO_BYTES = {              # (FP64, FP32) bytes per finest-level node
 # first half-sweep (FP64) or the residual the FP32 cycle casts (mixed): u,
 # psi, f read, one vector written
 NORM_SWEEP_BYTES = 80.0
+# Levels whose vectors have split rows during a solve (FP64: wider than 96 nodes,
+# FP32 V-cycles: wider than 192): a half-sweep reads u, psi and half of f and writes
+# half of u; the V-cycle iteration's convergence test writes half a vector (FP64) or
+# the FP32 load (mixed); the sweep from zero reads psi and f and writes u in two halves,
+# the second of which reads psi and the first half again
+SPLIT_BYTES = {"smooth": (56.0, 28.0), "norm": (68.0, 68.0), "sweep0": (76.0, 38.0)}
+SPLIT_KERNEL = ("k_rb_split<double, CoefCubic<double>, 0> (finest-level Gauss-Seidel "
+                "half-sweep on split rows")
 
 
 def _workload(name):
@@ -273,7 +281,7 @@ def _bench_j2(args):
     S.profile(False)
     ms_s, n_s = prof["smooth"]
     avg_ms = ms_s / max(n_s, 1)
-    by = ALGO_BYTES["smooth"][0] * nodes
+    by = SPLIT_BYTES["smooth"][0] * nodes
     achieved = by / (avg_ms * 1e-3) / 1e9
 
     def timed(make, reps=10):
@@ -317,8 +325,7 @@ def _bench_j2(args):
                    "yielding_cells": npl, "applied_displacement": state["d"]},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "k_rb_tile<double, ..., false, false> (LDS-tiled finest-level "
-                               "Gauss-Seidel half-sweep; 129 nodes in x)",
+                     "kernel": SPLIT_KERNEL + "; 129 nodes in x)",
                      "algo_bytes_per_launch": by, "avg_launch_us": avg_ms * 1e3,
                      "timing": "HIP events around each finest-level launch, one profiled solve "
                                "after the timed steps"},
@@ -472,7 +479,9 @@ def _bench_pf(args):
                    "intact_cells": n_intact},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "k_rb_half<double,2,false> (finest-level Gauss-Seidel half-sweep)",
+                     "kernel": "k_leg2<down/up, 2, 32> (a leg of the V-cycle's finest level: four "
+                               "Gauss-Seidel half-sweeps with residual and restriction, or with "
+                               "prolongation)",
                      "algo_bytes_per_launch": by, "avg_launch_us": avg_ms * 1e3,
                      "timing": "HIP events around each finest-level launch, one profiled solve "
                                "after the timed steps"},
@@ -558,7 +567,7 @@ def _bench_pressure(args):
     S.profile(False)
     ms_s, n_s = prof["smooth"]
     avg_ms = ms_s / max(n_s, 1)
-    by = ALGO_BYTES["smooth"][0] * nodes
+    by = SPLIT_BYTES["smooth"][0] * nodes
     achieved = by / (avg_ms * 1e-3) / 1e9
     ts = []
     for _ in range(10):
@@ -588,8 +597,7 @@ def _bench_pressure(args):
                    "final_rel_residual": max(fin), "status": sts},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "k_rb_tile<double, ..., false, false> (LDS-tiled finest-level "
-                               "Gauss-Seidel half-sweep; 129 nodes in x)",
+                     "kernel": SPLIT_KERNEL + "; 129 nodes in x)",
                      "algo_bytes_per_launch": by, "avg_launch_us": avg_ms * 1e3,
                      "timing": "HIP events around each finest-level launch, one profiled solve "
                                "after the timed steps"},
@@ -616,8 +624,10 @@ def _bench_pressure(args):
     print(json.dumps(line), flush=True)
 
 
-# 2D finest half-sweep: u (16), psi (8), f (16) read, u (16) written per node
-PF_SMOOTH_BYTES = 56.0
+# 2D legs of the finest level, from zero in a CG cycle: down psi 8, f 16 read, u 16 and
+# the coarse load 4 written; up u 16, psi 8, f 16 and the coarse correction 4 read, u 16
+# written: 52 B per node and launch on average
+PF_SMOOTH_BYTES = 52.0
 
 
 def _free_dof(p):
@@ -921,7 +931,12 @@ def main():
     triad = _triad()
     print(f"[bench] triad: {triad['GBps']:.0f} GB/s", file=sys.stderr, flush=True)
 
-    def kstats(prof, fp32, fused_norm=False):
+    # the library's thresholds: split rows in FP64 from 97 nodes in x, in FP32 V-cycles
+    # from 193 (and the fused r.z), natural rows in the mixed CG
+    wide = p.dim == 3 and p.ncell[0] + 1 > 192 and p.ncell[1] + 1 > 24
+    split64 = p.dim == 3 and p.ncell[0] + 1 > 96 and p.ncell[1] + 1 > 24
+
+    def kstats(prof, fp32, fused_norm=False, split=False):
         out = {}
         for k, (ms, n) in prof.items():
             if n == 0:
@@ -930,7 +945,9 @@ def main():
             ent = {"launches": n, "avg_us": avg * 1e3}
             if k in ALGO_BYTES:
                 by = ALGO_BYTES[k][1 if fp32 and k != "norm" else 0] * nodes
-                if k == "norm" and fused_norm:
+                if split and k in SPLIT_BYTES and (k != "norm" or fused_norm):
+                    by = SPLIT_BYTES[k][1 if fp32 else 0] * nodes
+                elif k == "norm" and fused_norm:
                     by = NORM_SWEEP_BYTES * nodes  # the norm pass also writes a half-sweep
                 ent["algo_GBps"] = by / (avg * 1e-3) / 1e9
                 ent["frac_hbm_peak"] = ent["algo_GBps"] / HBM_PEAK_GBS
@@ -946,18 +963,14 @@ def main():
                 "contraction_per_iteration": fin ** (1.0 / n_it) if n_it > 0 else None,
                 "final_rel_residual": fin, "status": r["st"],
                 "rel_l2_vs_fp64_solution": r["err"], "speedup_vs_headline": t64 / r["t"],
-                "kernels": kstats(r["prof"], r["prec"] == 1,
-                                  fused_norm=(r["kry"] == 0 and not tiled))}
+                "kernels": kstats(r["prof"], r["prec"] == 1, fused_norm=r["kry"] == 0,
+                                  split=split64 if r["prec"] == 0 else wide and r["kry"] == 0)}
 
     ms_s, n_s = prof64["smooth"]
     avg_ms = ms_s / max(n_s, 1)
-    by = ALGO_BYTES["smooth"][0] * nodes
+    by = (SPLIT_BYTES if split64 else ALGO_BYTES)["smooth"][0] * nodes
     achieved = by / (avg_ms * 1e-3) / 1e9
-    # the library's thresholds: half-sweeps go tiled from 97 nodes in x, the
-    # other finest-level passes (and the fused r.z) from 193
-    tiled = p.ncell[0] + 1 > 192 and p.dim == 3
-    tiled_sweep = p.ncell[0] + 1 > 96 and p.dim == 3
-    traffic = _traffic("k_rb_tile<double,false>" if tiled_sweep else TRAFFIC_KERNEL, nodes)
+    traffic = None if split64 else _traffic(TRAFFIC_KERNEL, nodes)
     line = {
         "metric": METRIC,
         "value": free / t64,
@@ -980,18 +993,17 @@ def main():
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "measured_triad_GBps": triad["GBps"],
                      "frac_of_measured_triad": achieved / triad["GBps"],
-                     "kernel": (("k_rb_tile<double, CoefCubic<double>, false, false> (LDS-tiled "
-                                 "finest-level Gauss-Seidel half-sweep" +
+                     "kernel": ((SPLIT_KERNEL +
                                  ("; the cycle's last one, which also sums r.z, is timed apart as "
-                                  "smooth_dot)" if tiled and head != "fp64" else ")"))
-                                if tiled_sweep else
+                                  "smooth_dot)" if head != "fp64" else ")"))
+                                if split64 else
                                 "k_rb_half<double,3,false> (finest-level Gauss-Seidel half-sweep)"),
                      "algo_bytes_per_launch": by, "avg_launch_us": avg_ms * 1e3,
                      "timing": "HIP events on the solver's stream around each finest-level launch "
                                "of one profiled solve after the timed region (launched one by "
                                "one: %.2f ms/solve)" % (tp64 * 1e3)},
         "triad": triad,
-        "kernels_fp64": kstats(prof64, False, fused_norm=(head == "fp64" and not tiled)),
+        "kernels_fp64": kstats(prof64, False, fused_norm=head == "fp64", split=split64),
         "variants": {name: vstats(r) for name, r in runs.items()},
     }
     for r in runs.values():

@@ -104,6 +104,8 @@ typedef struct {
  *   rtol           stop when ||f - K u||_2 <= rtol ||f||_2 over free DOF [1e-10]
  *   max_cycles     V-cycle cap [200]
  *   bottom_rtol    CG tolerance on the bottom grid, relative [1e-12]
+ *                  (FP64 cycles with 1e-13 to 1e-12 and no cap may solve the bottom
+ *                  by its inverse, formed to 1e-2 of it)
  *   bottom_max_iter CG iteration cap; <= 0 means 4 x free bottom DOF [0]
  *   use_graphs     1: each V-cycle is captured once into a HIP graph and
  *                  replayed (same kernels, same order, fewer launches) [1];

@@ -11,7 +11,8 @@
 // the state at its start (all new values are held in registers until every
 // thread has read its neighbours), which is the frozen-copy rule of the
 // per-kernel half-sweep without a second buffer.  The bottom CG runs in the
-// first wave alone (reductions by DPP, no barriers).
+// first wave alone (reductions by DPP, no barriers).  FP64 cycles near the
+// default bottom_rtol apply the bottom's inverse instead, formed once per problem.
 #include <algorithm>
 
 #include "sbm_bottom.h"
