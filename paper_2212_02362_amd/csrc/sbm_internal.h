@@ -292,6 +292,10 @@ int tail_level(const std::vector<Level> &L, int precision, size_t lds_max);
 hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void *dev,
                        double *dense_A, const double *inv, const int *inv_state,
                        size_t lds_max, size_t *lds_bytes, hipStream_t st);
+// A whole sweep (both colours) of a small 3D level, natural rows, FP64: xout (another
+// buffer than xin; xin NULL: zero) = xin relaxed (sbm_sweep3.hip).
+hipError_t launch_sweep3(const Level &L, const double *xin, const double *f, double *xout,
+                         double omega, int first_colour, hipStream_t st);
 // The legs of a 2D FP64 V-cycle on level L over Lc (sbm_leg2d.hip), nu 1 or 2
 // sweeps, xout another buffer than xin.  Down: xout = xin (NULL: zero) smoothed from
 // first_colour, fc = the restricted residual, ec (nullable) = 0.  Up: xout = xin +

@@ -402,6 +402,16 @@ struct RowsScope {
   }
 };
 
+// Whether a level's sweeps are one launch each: where two half-sweeps are bound by
+// latency (sweep against two half-sweeps: 17^3 5.2 / 9.5 us, 33^3 6.9 / 9.4 us; at
+// 65^3 the halos' work shows, 24 / 18 us).  Coarse levels: the finest one's first
+// half-sweep may be made by the convergence test, and live timing counts its
+// half-sweeps.
+static bool sweep3_ok(const sbm_ctx *c, int l) {
+  const Level &L = c->L[l];
+  return l > 0 && L.g.dim == 3 && L.g.hx == 0 && c->opt.fused_sweep == 0 && L.g.nn <= 50000;
+}
+
 // nu Gauss-Seidel sweeps on a level with split rows.  A half-sweep writes its
 // colour into the buffer that does not hold it, so a sweep moves the whole state
 // from one buffer to the other.
@@ -472,6 +482,19 @@ static hipError_t smooth(sbm_ctx *c, int l, T *x, const T *f, T *tmp, int nu, bo
   }
   if (L.g.hx) return smooth_split<T>(c, l, x, f, tmp, nu, reverse, pre);
   const int c0 = reverse ? 1 : 0;
+  if constexpr (sizeof(T) == 8) {
+    if (sweep3_ok(c, l) && nu > 0 && (pre || nu % 2 == 0)) {
+      // sweep by sweep from one buffer to the other, the last one into x; a coarse
+      // correction starts from zero
+      const T *cur = pre ? nullptr : x;
+      for (int s = 0; s < nu; ++s) {
+        T *dst = (nu - 1 - s) % 2 == 0 ? x : tmp;
+        if ((e = launch_sweep3(L, cur, f, dst, om, c0, c->st)) != hipSuccess) return e;
+        cur = dst;
+      }
+      return hipSuccess;
+    }
+  }
   // the finest level starts from zero when the caller says so (zero_start);
   // a coarser level always does on its pre-smoothing (its correction is the
   // zero the restriction wrote)
