@@ -1766,8 +1766,9 @@ __global__ __launch_bounds__(kBlock) void k_zero_split(GeomS g, Coef<T> C,
   const uint32_t fb = face_bits(g, i, j, k);
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const T w = ((g.dmask >> c) & fb) ? T(0) : omega;
-    t[c * g.nn + id] = T(0) + w * (fv[c] - T(0)) / dg[c];
+    // (a displacement DOF may have no solid around it: a zero diagonal)
+    const T upd = omega * fv[c] / dg[c];
+    t[c * g.nn + id] = ((g.dmask >> c) & fb) ? T(0) : upd;
   }
 }
 

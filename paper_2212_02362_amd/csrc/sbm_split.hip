@@ -314,7 +314,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         const bool fixed = ((g.dmask >> c) & fb) != 0u;
         T uc = T(0);
         if constexpr (!ZERO) uc = U(c, 0, 0, 0);
-        const T nv = uc + (fixed ? T(0) : omega) * (fr[q][c] - out[c]) / dg[c];
+        // (a displacement DOF may have no solid around it: a zero diagonal)
+        const T upd = uc + omega * (fr[q][c] - out[c]) / dg[c];
+        const T nv = fixed ? uc : upd;
         bstore<T>(nv, rout, vo, so + c * nn * W);
         if constexpr (DOT) {
           // f . u_out at both nodes of the pair (a node outside the box adds nothing)

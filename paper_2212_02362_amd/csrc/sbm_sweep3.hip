@@ -103,8 +103,9 @@ __global__ __launch_bounds__(NT3) void k_sweep3(Geom g, CO C, const double *__re
     const uint32_t bits = face_bits(g, gx0 + n[0], gy0 + n[1], gz0 + n[2]);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const double w = ((g.dmask >> c) & bits) ? 0.0 : omega;
-      nv[c] = U(c, 0, 0, 0) + w * (fv[c] - out[c]) / dg[c];
+      // (a displacement DOF may have no solid around it: a zero diagonal)
+      const double uc = U(c, 0, 0, 0), upd = uc + omega * (fv[c] - out[c]) / dg[c];
+      nv[c] = ((g.dmask >> c) & bits) ? uc : upd;
     }
   };
   double nv[3];

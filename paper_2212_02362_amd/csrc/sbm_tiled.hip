@@ -480,11 +480,15 @@ __device__ __forceinline__ void full_face_block(const TG &g, const CO &C, const 
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         const T val = KU ? out[c] : f[c * nn + q] - out[c];
-        v[c] = MODE != 4 && tg_dirichlet(g, x, y, z, c) ? T(0) : val;
+        const bool fixed = MODE != 4 && tg_dirichlet(g, x, y, z, c);
+        v[c] = fixed ? T(0) : val;
         if (!KU) acc += (double)v[c] * (double)v[c];
         else acc += (double)uc[c] * (double)v[c];
-        if (MODE == 3 && ((x + y + z) & 1) == co.colour)
-          co.half[c * nn + q] = uc[c] + co.omega * v[c] / dg[c];
+        if (MODE == 3 && ((x + y + z) & 1) == co.colour) {
+          // (a displacement DOF may have no solid around it: a zero diagonal)
+          const T upd = uc[c] + (T)co.omega * v[c] / dg[c];
+          co.half[c * nn + q] = fixed ? uc[c] : upd;
+        }
       }
     }
 #pragma unroll
@@ -617,7 +621,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
           v[c] = fixed ? T(0) : val;
           if (!KU) acc += (double)v[c] * (double)v[c];
           else if (MODE == 1) acc += (double)L0[c * PLANE + cu] * (double)v[c];
-          if constexpr (MODE == 3) v[c] = L0[c * PLANE + cu] + (T)co.omega * v[c] / dg[c];
+          if constexpr (MODE == 3) {
+            const T uc = L0[c * PLANE + cu], upd = uc + (T)co.omega * v[c] / dg[c];
+            v[c] = fixed ? uc : upd;
+          }
         }
       }
       // without r the descriptor is empty and the stores are dropped (a branch
