@@ -105,7 +105,8 @@ typedef struct {
  *   max_cycles     V-cycle cap [200]
  *   bottom_rtol    CG tolerance on the bottom grid, relative [1e-12]
  *                  (FP64 cycles with 1e-13 to 1e-12 and no cap may solve the bottom
- *                  by its inverse, formed to 1e-2 of it)
+ *                  by its inverse: kept where f - K x itself is within bottom_rtol
+ *                  of f or within the rounding of K x, else the CG runs)
  *   bottom_max_iter CG iteration cap; <= 0 means 4 x free bottom DOF [0]
  *   use_graphs     1: each V-cycle is captured once into a HIP graph and
  *                  replayed (same kernels, same order, fewer launches) [1];

@@ -54,6 +54,31 @@ __device__ __forceinline__ void bot_allsum2(double &v0, double &v1, BotRed &R) {
   v1 = s1;
 }
 
+// Three sums in every thread, one barrier (buf: 3 doubles per wave, not read by
+// threads that are behind an earlier barrier).
+__device__ __forceinline__ void bot_allsum3(double (&v)[3], double *buf) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) v[q] = wave_sum(v[q]);
+  const int nw = blockDim.x >> 6;
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) buf[q * nw + (threadIdx.x >> 6)] = v[q];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    v[q] = 0.0;
+    for (int w = 0; w < nw; ++w) v[q] += buf[q * nw + w];
+  }
+}
+
+// Whether a bottom solution found without the CG stands for the CG's: by its own
+// residual, from the sums of (f - K x)^2, f^2 and (D x)^2, D the diagonal.  Either
+// the CG's tolerance, or the rounding of K x itself, where no method's residual ends
+// lower (the CG's neither: solutions large against their load, as behind a floor layer).
+__device__ __forceinline__ bool bottom_solved(const double (&s)[3], double rtol) {
+  return s[0] <= rtol * rtol * s[1] || s[0] <= 0x1p-104 * s[2];
+}
+
 // Jacobi-preconditioned CG on K_FF d = r (d from 0) with p and psi in LDS;
 // r, d and the inverse diagonal in registers.  Stops when
 // ||r|| <= rtol ||r0||.  Returns the iterations; d holds the increment.

@@ -307,13 +307,14 @@ hipError_t launch_leg2_up(const Level &L, const Level &Lc, const double *xin, co
                           double *xout, const double *e, double omega, int first_colour, int nu,
                           hipStream_t st);
 // The inverse of the bottom operator ((DOF)^2 values), a column per workgroup by
-// the bottom CG to a relative residual of tol; state (two ints, 0 on entry): [0]
-// is set when it is formed, [1] when a column misses tol.
+// the bottom CG to an updated residual of tol; state (two ints, 0 on entry): [0]
+// is set when it is formed, [1] when a column's own residual is too large to refine.
 hipError_t launch_bottom_inverse(const Level &B, double *inv, int *state, double tol, int maxit,
                                  hipStream_t st);
-// x = inv f, where the state says that inv is there.
-hipError_t launch_bottom_product(const Level &B, const double *inv, const int *state,
-                                 const double *f, double *x, hipStream_t st);
+// x = inv f, refined once unless its residual is that of a solve to rtol, where the
+// state says that inv is there (y: scratch of the bottom's size).
+hipError_t launch_bottom_product(const Level &B, const double *inv, const int *state, double rtol,
+                                 const double *f, double *y, double *x, hipStream_t st);
 template <typename T>
 hipError_t launch_tail(int dim, bool wide_bottom, const void *dev, size_t lds_bytes,
                        T *x, const T *f, const TailOpts &o, int *iters, hipStream_t st);

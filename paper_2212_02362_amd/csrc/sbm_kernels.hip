@@ -1138,7 +1138,8 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom_cg(Geom g, Coef<T> C,
 // (CG core and reductions in sbm_bottom.h)
 
 // FP64 bottom: x += CG solution of K_FF d = (f - K x)_F.  f and x are FP64,
-// or FP32 in the mixed cycle (read into and written from the FP64 solve).
+// or FP32 in the mixed cycle (read into and written from the FP64 solve).  Where the
+// state says that the inverse made x, only its residual is looked at (bottom_solved).
 template <int DIM, int Q, typename IO>
 __global__ __launch_bounds__(kBotThreads) void k_bottom_lds64(Geom g, Coef<double> C,
                                                        const double *__restrict__ psi,
@@ -1146,7 +1147,6 @@ __global__ __launch_bounds__(kBotThreads) void k_bottom_lds64(Geom g, Coef<doubl
                                                        double rtol, int maxit, int *iters,
                                                        const int *inv_state) {
   extern __shared__ double smem[];
-  if (inv_state && inv_state[0] != 0 && inv_state[1] == 0) return;  // solved by the inverse
   __shared__ double red[64];
   BotRed R{red, 0};
   const int64_t n = g.nn;
@@ -1155,7 +1155,7 @@ __global__ __launch_bounds__(kBotThreads) void k_bottom_lds64(Geom g, Coef<doubl
   for (int64_t q = threadIdx.x; q < g.nc; q += blockDim.x) psi_l[q] = psi[q];
   bool dir[Q][3];
   int cijk[Q][3];
-  double r[Q][3], dd[Q][3], xv[Q][3];
+  double r[Q][3], dd[Q][3], xv[Q][3], sum[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int64_t id = threadIdx.x + (int64_t)q * blockDim.x;
@@ -1182,9 +1182,34 @@ __global__ __launch_bounds__(kBotThreads) void k_bottom_lds64(Geom g, Coef<doubl
     double out[3], dg[3];
     node_stencil<double, DIM>(g, C, psi_l, p_l, cijk[q][0], cijk[q][1], cijk[q][2], out, dg);
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) r[q][c] = dir[q][c] ? 0.0 : (double)f[c * n + id] - out[c];
+    for (int c = 0; c < DIM; ++c) {
+      const double fv = dir[q][c] ? 0.0 : (double)f[c * n + id];
+      const double dx = dir[q][c] ? 0.0 : dg[c] * xv[q][c];
+      r[q][c] = dir[q][c] ? 0.0 : fv - out[c];
+      sum[0] += r[q][c] * r[q][c];
+      sum[1] += fv * fv;
+      sum[2] += dx * dx;
+    }
   }
   __syncthreads();
+  if (inv_state && inv_state[0] != 0 && inv_state[1] == 0) {
+    // x comes from the inverse: it stands, or the CG starts from zero
+    bot_allsum3(sum, red);
+    if (bottom_solved(sum, rtol)) {
+      if (threadIdx.x == 0 && iters) *iters = 1;
+      return;
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int64_t id = threadIdx.x + (int64_t)q * blockDim.x;
+#pragma unroll
+      for (int c = 0; c < DIM; ++c) {
+        xv[q][c] = 0.0;
+        if (id < n) r[q][c] = dir[q][c] ? 0.0 : (double)f[c * n + id];
+      }
+    }
+    __syncthreads();
+  }
   const int it = bot_cg<double, DIM, Q>(g, C, psi_l, p_l, r, dd, dir, cijk, rtol, maxit, R);
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
@@ -1809,6 +1834,7 @@ static int bottom_threads(int64_t nn) {
   return (int)(t < 64 ? 64 : (t > kBotThreads ? kBotThreads : t));
 }
 
+static_assert(kInverseNodes <= kBotQ * kBotThreads, "its check is in the LDS-resident kernel");
 static bool bottom_fits_lds(const Geom &g, size_t bytes) {
   return g.nn <= (int64_t)kBotQ * kBotThreads && bytes <= 64 * 1024;
 }

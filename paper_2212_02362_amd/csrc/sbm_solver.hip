@@ -596,12 +596,13 @@ static void rz_set(sbm_ctx *c, const double *ss, bool fp64 = false) {
 }
 
 static bool inverse_ok(const sbm_ctx *c);
-// cycle: x is 0 on entry (the inverse may stand for the CG).
+// cycle: x is 0 on entry (the inverse may stand for the CG, if its residual does).
 static hipError_t bottom64(sbm_ctx *c, const double *f, double *x, bool cycle) {
   Level &B = c->L[c->nlev - 1];
   const int *state = cycle && inverse_ok(c) ? c->iflag + 13 : nullptr;
   hipError_t e;
-  if (state && (e = launch_bottom_product(B, c->tail_inv, state, f, x, c->st)) != hipSuccess)
+  if (state && (e = launch_bottom_product(B, c->tail_inv, state, c->opt.bottom_rtol, f, c->b_r, x,
+                                          c->st)) != hipSuccess)
     return e;
   return launch_bottom_cg<double>(B, B.psi64, B.c64, f, x, c->b_r, c->b_p, c->b_Ap,
                                   c->opt.bottom_rtol, bottom_maxit(c), c->iflag + 4, c->st, state);
@@ -617,7 +618,8 @@ static hipError_t bottom32(sbm_ctx *c, const float *f, float *x) {
 // Whether FP64 cycles may apply the bottom's inverse: the bottom is a coarse level
 // (its iterate starts from zero) of at most kInverseNodes nodes, bottom_rtol is
 // near its default 1e-12 and the iterations are not capped.  Its columns are
-// solved to 1e-2 bottom_rtol, so a sum over 1536 of them keeps bottom_rtol.  A
+// solved until the CG's updated residual is 1e-2 bottom_rtol; each product is kept
+// only if its own residual is that of a solve, else the CG runs (bottom_solved).  A
 // looser CG is cheaper and stays.
 static bool inverse_ok(const sbm_ctx *c) {
   const Level &B = c->L.back();

@@ -12,7 +12,8 @@
 // thread has read its neighbours), which is the frozen-copy rule of the
 // per-kernel half-sweep without a second buffer.  The bottom CG runs in the
 // first wave alone (reductions by DPP, no barriers).  FP64 cycles near the
-// default bottom_rtol apply the bottom's inverse instead, formed once per problem.
+// default bottom_rtol apply the bottom's inverse instead, formed once per problem,
+// and keep the result if its own residual is that of a solve.
 #include <algorithm>
 
 #include "sbm_bottom.h"
@@ -58,8 +59,8 @@ struct TailArgs {
 };
 static_assert(sizeof(TailArgs<double>) <= kTailArgBytes, "tail table too large");
 
-// The state of the bottom's inverse: [0] it has been formed, [1] a column missed
-// its tolerance.
+// The state of the bottom's inverse: [0] it has been formed, [1] a column is too
+// far off to refine with.
 __device__ __forceinline__ bool inverse_there(const int *state) {
   return state[0] != 0 && state[1] == 0;
 }
@@ -82,6 +83,40 @@ __device__ __forceinline__ double inverse_row(const double *__restrict__ inv, in
     for (int q = 0; q < 16; ++q) acc += j + q < j1 ? v[q] * w[q] : 0.0;
   }
   return acc;
+}
+
+// The columns come from a CG that stops on its updated residual, whose own
+// residual stalls at the rounding of the contrast (a stiff part behind a layer of
+// psi 1e-6: 5e-9 of the unit load).  What is kept of a product is therefore decided
+// by its residual (bottom_solved), after steps x += inv (f - K x) if it is not there
+// at once; each leaves at most sqrt(1536) kColumnMiss of the residual.  Residuals
+// behind floor layers of 1e-3 .. 1e-9, extended precision, load K u / random: CG 6e-13
+// / 9e-13 .. 7e-7, product 7e-13 .. 9e-7 / 9e-13 .. 1e-6, one step 1e-16 .. 2e-12 /
+// 7e-14 .. 6e-8.
+constexpr double kColumnMiss = 1e-4;
+constexpr int kTailRefine = 2;
+
+// Adds a node's share to the sums of bottom_solved and returns f - K x (0 on
+// displacement DOF).
+template <int DIM>
+__device__ __forceinline__ void bottom_residual(const Geom &g, const Coef<double> &C,
+                                                const double *psi, const double *f,
+                                                const double *x, int id, double (&rv)[3],
+                                                double (&s)[3]) {
+  int i, j, k;
+  node_ijk(g, id, i, j, k);
+  const uint32_t fb = face_bits(g, i, j, k);
+  double out[3], dg[3];
+  node_stencil<double, DIM, false>(g, C, psi, x, i, j, k, out, dg);
+#pragma unroll
+  for (int c = 0; c < DIM; ++c) {
+    const bool dir = ((g.dmask >> c) & fb) != 0u;
+    const double fv = dir ? 0.0 : f[c * g.nn + id], dx = dir ? 0.0 : dg[c] * x[c * g.nn + id];
+    rv[c] = dir ? 0.0 : fv - out[c];
+    s[0] += rv[c] * rv[c];
+    s[1] += fv * fv;
+    s[2] += dx * dx;
+  }
 }
 
 // Wave-scope ordering of LDS accesses between lanes of one wave (the bottom
@@ -411,38 +446,52 @@ struct Tail {
     __syncthreads();
   }
 
-  // X(B) = K_B^-1 F(B) with the inverse of tail_inverse: thread (part s, row i)
-  // sums its share of the row, the parts are added in order.  It takes the
-  // place of a CG of some n3 dependent iterations of 1 to 2 us (bound by
-  // latency).  Bound by reading n3^2 values from L2; the whole tail with a
-  // bottom of 112 nodes 259 -> 48 us, of 27 nodes 59 -> 45 us.
-  __device__ __forceinline__ void bottom_inverse(int *iters) const {
-    const int n3 = a.n3, pitch = (n3 + 63) & ~63;
+  // X(B) = K_B^-1 F(B) with the inverse: thread (part s, row i) sums its share of
+  // the row, the parts are added in order; then the residual, and up to kTailRefine
+  // steps of refinement.  Returns whether that solves it; else the CG does.  It takes
+  // the place of a CG of some n3 dependent iterations of 1 to 2 us (bound by
+  // latency).  Bound by reading n3^2 values from L2.
+  __device__ __forceinline__ bool bottom_inverse(int *iters) const {
+    const int n3 = a.n3, n = (int)a.gb.nn, pitch = (n3 + 63) & ~63;
     const int s = threadIdx.x / pitch, i = threadIdx.x - s * pitch;
     const int len = (n3 + a.parts - 1) / a.parts;
     T *xb = (T *)(sm + a.oxb);
-    const T *fb_ = (const T *)(sm + a.ofb);
-    if (s < a.parts && i < n3) {
-      R()[s * n3 + i] = inverse_row(a.inv, n3, i, fb_, s * len, min(n3, (s + 1) * len));
-    }
-    __syncthreads();
-    if (threadIdx.x < n3) {
-      double v = 0.0;
-      for (int q = 0; q < a.parts; ++q) v += R()[q * n3 + threadIdx.x];
-      xb[threadIdx.x] = v;
+    const T *fb_ = (const T *)(sm + a.ofb), *rhs = fb_;
+    const double *psi = (const double *)(sm + a.opb);
+    double *rl = (double *)(sm + a.opp), *red = (double *)(sm + a.ored);
+    for (int step = 0;; ++step) {
+      if (s < a.parts && i < n3)
+        R()[s * n3 + i] = inverse_row(a.inv, n3, i, rhs, s * len, min(n3, (s + 1) * len));
+      __syncthreads();
+      if (threadIdx.x < n3) {
+        double v = 0.0;
+        for (int q = 0; q < a.parts; ++q) v += R()[q * n3 + threadIdx.x];
+        xb[threadIdx.x] = step > 0 ? xb[threadIdx.x] + v : v;
+      }
+      __syncthreads();
+      double rv[3], sum[3] = {0.0, 0.0, 0.0};
+      if (threadIdx.x < n) {
+        bottom_residual<DIM>(a.gb, a.Cb, psi, fb_, xb, threadIdx.x, rv, sum);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) rl[c * n + threadIdx.x] = rv[c];
+      }
+      bot_allsum3(sum, red);
+      if (bottom_solved(sum, o.rtol)) break;
+      if (step == kTailRefine) {
+        __syncthreads();  // the CG reduces in the same LDS
+        return false;
+      }
+      rhs = rl;
     }
     if (threadIdx.x == 0 && iters) *iters = 1;
-    __syncthreads();
+    return true;
   }
 
   // X(B) = CG(K_B, F(B)) from zero, in FP64 in the first wave: Jacobi
   // preconditioning, stop at ||r|| <= rtol ||r0|| or maxit iterations.
   __device__ __forceinline__ void bottom(int *iters) const {
     if constexpr (sizeof(T) == 8) {
-      if (o.inverse && inverse_there(a.inv_state)) {
-        bottom_inverse(iters);
-        return;
-      }
+      if (o.inverse && inverse_there(a.inv_state) && bottom_inverse(iters)) return;
     }
     if constexpr (WIDE) {
       bottom_wide(iters);
@@ -659,38 +708,79 @@ __global__ __launch_bounds__(kTailThreads) void k_bottom_inverse(
   __syncthreads();
   // (a displacement DOF: zero load, zero column)
   bot_cg<double, DIM, 1, false>(g, C, psi, p, r, d, dir, cijk, tol, maxit, R);
-  double rr = 0.0;
+  // the column's own residual (the updated one falls below any tolerance)
+  if (id < n)
 #pragma unroll
-  for (int c = 0; c < 3; ++c) rr += r[0][c] * r[0][c];
+    for (int c = 0; c < DIM; ++c) p[c * n + id] = d[0][c];
+  __syncthreads();
+  double rr = 0.0;
+  if (id < n) {
+    double ku[3], dg[3];
+    node_stencil<double, DIM, false>(g, C, psi, p, cijk[0][0], cijk[0][1], cijk[0][2], ku, dg);
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+      const double v = dir[0][c] ? 0.0 : (id == cn && c == cc ? 1.0 : 0.0) - ku[c];
+      rr += v * v;
+    }
+  }
   rr = bot_allsum(rr, R);
-  if (id == 0 && !(rr <= tol * tol)) state[1] = 1;
+  if (id == 0 && !(rr <= kColumnMiss * kColumnMiss)) state[1] = 1;
   if (id == 0 && col == 0) state[0] = 1;
   if (id < n)
 #pragma unroll
     for (int c = 0; c < DIM; ++c) out[c * n + id] = d[0][c];
 }
 
-// x = inverse f for a bottom outside the tail (the tail holds two levels or more
-// in LDS): 64 rows per workgroup, a wave per sixteenth of their sums.  Without an
-// inverse it leaves x as it is and the CG launched behind it does the work.
-// Bound by the latency of n3 / 16 loads in flight 16 at a time (512 nodes: 22 us,
-// the CG 420 us).
+// y = inverse f for a bottom outside the tail (the tail holds two levels or more
+// in LDS): 64 rows per workgroup, a wave per sixteenth of their sums.  Then x = y, or
+// the refined y + inverse (f - K y) where the residual of y is not that of a solve
+// (every workgroup forms it); the bottom kernel launched behind looks at that of x.
+// Without an inverse both leave x as it is.  Bound by the latency of n3 / 16 loads in
+// flight 16 at a time.
 constexpr int kProdParts = 16;
-__global__ __launch_bounds__(64 * kProdParts) void k_bottom_product(
-    int n3, const double *__restrict__ inv, const int *__restrict__ state,
-    const double *__restrict__ f, double *__restrict__ x) {
-  __shared__ double part[kProdParts][64];
-  if (!inverse_there(state)) return;
+__device__ __forceinline__ double product_row(int n3, const double *__restrict__ inv,
+                                              const double *f, double (*part)[64]) {
   const int lane = threadIdx.x & 63, s = threadIdx.x >> 6;
   const int i = blockIdx.x * 64 + lane, len = (n3 + kProdParts - 1) / kProdParts;
   part[s][lane] = i < n3 ? inverse_row(inv, n3, i, f, s * len, min(n3, (s + 1) * len)) : 0.0;
   __syncthreads();
-  if (s == 0 && i < n3) {
-    double v = 0.0;
+  double v = 0.0;
+  if (s == 0)
 #pragma unroll
     for (int q = 0; q < kProdParts; ++q) v += part[q][lane];
-    x[i] = v;
+  return v;  // in the first wave
+}
+
+__global__ __launch_bounds__(64 * kProdParts) void k_bottom_product(
+    int n3, const double *__restrict__ inv, const int *__restrict__ state,
+    const double *__restrict__ f, double *__restrict__ y) {
+  __shared__ double part[kProdParts][64];
+  if (!inverse_there(state)) return;
+  const double v = product_row(n3, inv, f, part);
+  const int i = blockIdx.x * 64 + threadIdx.x;
+  if (threadIdx.x < 64 && i < n3) y[i] = v;
+}
+
+template <int DIM>
+__global__ __launch_bounds__(64 * kProdParts) void k_bottom_refine(
+    Geom g, Coef<double> C, const double *__restrict__ psi, const double *__restrict__ inv,
+    const int *__restrict__ state, double rtol, const double *__restrict__ f,
+    const double *__restrict__ y, double *__restrict__ x) {
+  __shared__ double part[kProdParts][64];
+  __shared__ double rl[DIM * kInverseNodes];
+  __shared__ double red[3 * kProdParts];
+  if (!inverse_there(state)) return;
+  const int n = (int)g.nn, n3 = DIM * n;
+  double rv[3], sum[3] = {0.0, 0.0, 0.0};
+  if (threadIdx.x < n) {
+    bottom_residual<DIM>(g, C, psi, f, y, threadIdx.x, rv, sum);
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) rl[c * n + threadIdx.x] = rv[c];
   }
+  bot_allsum3(sum, red);
+  const double v = bottom_solved(sum, rtol) ? 0.0 : product_row(n3, inv, rl, part);
+  const int i = blockIdx.x * 64 + threadIdx.x;
+  if (threadIdx.x < 64 && i < n3) x[i] = y[i] + v;
 }
 
 template <typename T>
@@ -837,12 +927,19 @@ hipError_t launch_bottom_inverse(const Level &B, double *inv, int *state, double
   return hipGetLastError();
 }
 
-hipError_t launch_bottom_product(const Level &B, const double *inv, const int *state,
-                                 const double *f, double *x, hipStream_t st) {
-  const int n3 = B.g.dim * (int)B.g.nn;
+hipError_t launch_bottom_product(const Level &B, const double *inv, const int *state, double rtol,
+                                 const double *f, double *y, double *x, hipStream_t st) {
+  const int n = (int)B.g.nn, n3 = B.g.dim * n;
+  if (n > kInverseNodes) return hipErrorInvalidValue;
+  const dim3 grid((n3 + 63) / 64), block(64 * kProdParts);
   (void)hipGetLastError();
-  hipLaunchKernelGGL(k_bottom_product, dim3((n3 + 63) / 64), dim3(64 * kProdParts), 0, st, n3, inv,
-                     state, f, x);
+  hipLaunchKernelGGL(k_bottom_product, grid, block, 0, st, n3, inv, state, f, y);
+  if (B.g.dim == 3)
+    hipLaunchKernelGGL(k_bottom_refine<3>, grid, block, 0, st, B.g, B.c64, B.psi64, inv, state,
+                       rtol, f, y, x);
+  else
+    hipLaunchKernelGGL(k_bottom_refine<2>, grid, block, 0, st, B.g, B.c64, B.psi64, inv, state,
+                       rtol, f, y, x);
   return hipGetLastError();
 }
 
