@@ -286,7 +286,7 @@ struct TailOpts {
   int nu_pre, nu_post, jacobi, reverse;
   double omega, rtol;
   int maxit;
-  int inverse;  // FP64: apply the bottom's inverse where its state says it is there
+  int inverse;  // FP64: apply the bottom's inverse where its state says so
 };
 int tail_level(const std::vector<Level> &L, int precision, size_t lds_max);
 hipError_t tail_upload(const std::vector<Level> &L, int precision, int l0, void *dev,
@@ -307,12 +307,13 @@ hipError_t launch_leg2_up(const Level &L, const Level &Lc, const double *xin, co
                           double *xout, const double *e, double omega, int first_colour, int nu,
                           hipStream_t st);
 // The inverse of the bottom operator ((DOF)^2 values), a column per workgroup by
-// the bottom CG to an updated residual of tol; state (two ints, 0 on entry): [0]
-// is set when it is formed, [1] when a column's own residual is too large to refine.
+// the bottom CG to an updated residual of tol; state (two ints, 0 on entry): [1] is set
+// when a column's own residual is too large to refine; [0] is the caller's, nonzero
+// where cycles are to use it.
 hipError_t launch_bottom_inverse(const Level &B, double *inv, int *state, double tol, int maxit,
                                  hipStream_t st);
 // x = inv f, refined once unless its residual is that of a solve to rtol, where the
-// state says that inv is there (y: scratch of the bottom's size).
+// state says that inv is in use (y: scratch of the bottom's size).
 hipError_t launch_bottom_product(const Level &B, const double *inv, const int *state, double rtol,
                                  const double *f, double *y, double *x, hipStream_t st);
 template <typename T>

@@ -123,6 +123,7 @@ struct sbm_ctx {
   // inverse of the bottom operator (FP64 cycles), its state in iflag[13], [14]
   double *tail_inv = nullptr;
   bool inv_ready = false;  // formed for the current problem and options
+  bool inv_on = false;     // iflag[13]: cycles use it
   size_t tail_lds64 = 0, tail_lds32 = 0;
   size_t tail_lds_max = 64 * 1024;  // LDS bytes a workgroup may hold on this device
   // set while a cycle runs whose first finest-level half-sweep was already
@@ -628,22 +629,34 @@ static bool inverse_ok(const sbm_ctx *c) {
          c->opt.bottom_rtol >= 1e-13 && c->opt.bottom_rtol <= 1e-12;
 }
 
-// Forms the inverse once per problem, before cycle m (0 the first): as many CG
-// solves as DOF side by side, where each cycle would make one.  Up to 512 DOF they
-// take little more than one (112 nodes: 247 us against 215 us per cycle); larger
-// bottoms take a few (512 nodes: 1530 against 420 us), so theirs waits for a second
-// cycle (with it: 28^3 cells 9.7 -> 4.4 ms, 56x40x48 10.9 -> 5.2 ms).
-static hipError_t prepare_inverse(sbm_ctx *c, int m) {
-  const Level &B = c->L.back();
-  if (c->inv_ready || c->opt.precision != 0 || !inverse_ok(c) ||
-      (m < 1 && c->dim * B.g.nn > kTailInverse))
-    return hipSuccess;
-  c->inv_ready = true;
-  return launch_bottom_inverse(B, c->tail_inv, c->iflag + 13, 1e-2 * c->opt.bottom_rtol,
-                               2 * bottom_maxit(c), c->st);
+// Cycles of a solve before its inverse is formed (once per problem, as many CG solves
+// as DOF side by side) and used: as many as it costs, so a solve of few cycles pays
+// for none and one that goes on pays at most twice its CGs.  Up to 512 DOF forming
+// takes little more than one CG (112 nodes: 247 against 215 us); larger bottoms take a
+// few (512 nodes: 1530 against 420 us).  The rule looks at the cycle alone, not at
+// whether an earlier solve has formed it: repeated solves make the same steps.
+static int cycles_before_inverse(const sbm_ctx *c) {
+  return c->dim * c->L.back().g.nn <= kTailInverse ? 1 : 4;
 }
 
-hipError_t sbm::base_prepare(sbm_ctx *c) { return prepare_inverse(c, 1); }
+// Before cycle m (0 the first) of a solve: switches the inverse on or off.
+static hipError_t prepare_inverse(sbm_ctx *c, int m) {
+  if (c->opt.precision != 0 || !inverse_ok(c)) return hipSuccess;
+  const bool on = m >= cycles_before_inverse(c);
+  hipError_t e;
+  if (on && !c->inv_ready) {
+    if ((e = launch_bottom_inverse(c->L.back(), c->tail_inv, c->iflag + 13,
+                                   1e-2 * c->opt.bottom_rtol, 2 * bottom_maxit(c), c->st)) !=
+        hipSuccess)
+      return e;
+    c->inv_ready = true;
+  }
+  if (on == c->inv_on) return hipSuccess;
+  c->inv_on = on;
+  return launch_fill<int>(c->iflag + 13, 1, on ? 1 : 0, c->st);
+}
+
+hipError_t sbm::base_prepare(sbm_ctx *c) { return prepare_inverse(c, cycles_before_inverse(c)); }
 
 // Whether level l runs its legs of a FP64 V-cycle in one launch each: 2D, one or two
 // sweeps on either leg (the halo of more would outgrow the tile), above the tail,
@@ -1270,7 +1283,7 @@ sbm_status sbm_set_options(sbm_ctx *c, const sbm_options *opts) {
   if (!same) {
     HIP_TRY(hipStreamSynchronize(c->st));
     drop_graphs(c);
-    c->inv_ready = false;
+    c->inv_ready = c->inv_on = false;
     HIP_TRY(launch_fill<int>(c->iflag + 13, 2, 0, c->st));
   }
   c->opt = *opts;
@@ -1443,12 +1456,12 @@ static sbm_status set_problem_impl(sbm_ctx *c, const double *psi_raw, int cube,
     set_coefs(c->L[l], mat->lambda, mat->mu, c->dim);
   }
   Level &L0 = c->L[0];
+  c->inv_ready = c->inv_on = false;
   HIP_TRY(launch_fill<int>(c->iflag, 16, 0, c->st));
   HIP_TRY(launch_floor_psi(psi_raw, mat->psi_floor, L0.psi64, L0.psi32, L0.g.nc, cube, c->iflag,
                            c->st));
   for (int l = 1; l < c->nlev; ++l) HIP_TRY(launch_coarsen_psi(c->L[l - 1], c->L[l], c->st));
   // tail level tables and the dense bottom matrix (needs the bottom psi)
-  c->inv_ready = false;
   if (c->tail64 >= 0)
     HIP_TRY(tail_upload(c->L, 0, c->tail64, c->tail_args, c->tail_A, c->tail_inv, c->iflag + 13,
                         c->tail_lds_max, &c->tail_lds64, c->st));

@@ -59,7 +59,7 @@ struct TailArgs {
 };
 static_assert(sizeof(TailArgs<double>) <= kTailArgBytes, "tail table too large");
 
-// The state of the bottom's inverse: [0] it has been formed, [1] a column is too
+// The state of the bottom's inverse: [0] it is formed and in use, [1] a column is too
 // far off to refine with.
 __device__ __forceinline__ bool inverse_there(const int *state) {
   return state[0] != 0 && state[1] == 0;
@@ -725,7 +725,6 @@ __global__ __launch_bounds__(kTailThreads) void k_bottom_inverse(
   }
   rr = bot_allsum(rr, R);
   if (id == 0 && !(rr <= kColumnMiss * kColumnMiss)) state[1] = 1;
-  if (id == 0 && col == 0) state[0] = 1;
   if (id < n)
 #pragma unroll
     for (int c = 0; c < DIM; ++c) out[c * n + id] = d[0][c];
