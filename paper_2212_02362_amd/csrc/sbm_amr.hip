@@ -1697,7 +1697,6 @@ sbm_status sbm_amr_set_problem(sbm_amr_ctx *c, const double *const *psi_raw,
   if (flags & 2) return amr_fail(SBM_E_DIAG, "a free DOF has no solid cell around it");
   // uniform hierarchy of the base level on the averaged-down psi
   AMR_TRY(sbm_set_problem(c->base, c->lv[0].L.psi64, mat, bc, nullptr));
-  AMR_HIP(base_prepare(c->base));
   // ||lifted load||: composite residual of the prescribed values
   double *x[kMaxAmrLevels], *f[kMaxAmrLevels], *r[kMaxAmrLevels];
   for (int a = 0; a <= A; ++a) {
@@ -1857,6 +1856,7 @@ sbm_status sbm_amr_solve(sbm_amr_ctx *c, double *const *u, double *hist_host, in
                                      a >= 1 ? c->lv[a].unknown_tiles() : nullptr));
     } else {
       for (int a = 0; a <= A; ++a) AMR_HIP(amr_zero<double>(c, c->lv[a], c->lv[a].e));
+      AMR_HIP(base_prepare(c->base, m));
       AMR_HIP(amr_fas<double>(c, A));
       for (int a = 0; a <= A; ++a)
         AMR_HIP(launch_update<double>(c->lv[a].L, a >= 1 ? c->lv[a].cls : nullptr, u[a],

@@ -355,7 +355,7 @@ void set_coefs(Level &L, double lam, double mu, int dim);
 // One V-cycle of the uniform hierarchy of c from its finest level: x (in/out)
 // and f are finest-level vectors in FP64 (precision 0) or FP32 (precision 1).
 hipError_t base_vcycle(sbm_ctx *c, int precision, void *x, const void *f);
-// Forms what its FP64 cycles use besides the problem.
-hipError_t base_prepare(sbm_ctx *c);
+// Before cycle m of a composite solve in FP64: what its FP64 cycles use besides the problem.
+hipError_t base_prepare(sbm_ctx *c, int m);
 
 }  // namespace sbm

@@ -656,7 +656,7 @@ static hipError_t prepare_inverse(sbm_ctx *c, int m) {
   return launch_fill<int>(c->iflag + 13, 1, on ? 1 : 0, c->st);
 }
 
-hipError_t sbm::base_prepare(sbm_ctx *c) { return prepare_inverse(c, cycles_before_inverse(c)); }
+hipError_t sbm::base_prepare(sbm_ctx *c, int m) { return prepare_inverse(c, m); }
 
 // Whether level l runs its legs of a FP64 V-cycle in one launch each: 2D, one or two
 // sweeps on either leg (the halo of more would outgrow the tile), above the tail,
