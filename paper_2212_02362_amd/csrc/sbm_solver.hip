@@ -388,14 +388,17 @@ static hipError_t half_sweep(const Level &L, const T *psi, const Coef<T> &C, con
 }
 
 // The vectors of a solve's wide levels have split rows (sbm_device.h) while it
-// runs; everything else sees natural rows.  Gauss-Seidel only; and the mixed CG
-// stays with natural rows: its Krylov scalars follow the rounding of the FP32
-// cycle, and another order of that arithmetic moves its residual history by 1e-9
-// (129-node rows) where FP64 cycles move by 1e-16.
+// runs; everything else sees natural rows.  Gauss-Seidel only, and not with
+// fused_sweep, whose one-launch sweep needs both colours of a row together; and the
+// mixed CG stays with natural rows: its Krylov scalars follow the rounding of the
+// FP32 cycle, and another order of that arithmetic moves its residual history by
+// 1e-9 (129-node rows) where FP64 cycles move by 1e-16.
 struct RowsScope {
   sbm_ctx *c;
   explicit RowsScope(sbm_ctx *c_) : c(c_) {
-    if (c->opt.smoother != 0 || (c->opt.precision == 1 && c->opt.krylov == 1)) return;
+    if (c->opt.smoother != 0 || c->opt.fused_sweep == 1 ||
+        (c->opt.precision == 1 && c->opt.krylov == 1))
+      return;
     for (Level &L : c->L) L.g.hx = c->opt.precision == 1 ? L.hx32 : L.hx64;
   }
   ~RowsScope() {
@@ -849,7 +852,7 @@ static hipError_t cycle_body(sbm_ctx *c, const double *f, int mode) {
     // the tail, its first half-sweep from zero is pointwise (omega kr / D on
     // one colour) and is made together with the cast or instead of the fill.
     const bool skip = c->opt.smoother == 0 && c->opt.nu_pre >= 1 && c->nlev > 1;
-    // mixed: a tiled finest level starts with the one-launch sweep from zero
+    // a tiled finest level on natural rows starts with the one-launch sweep from zero
     const bool zs = skip && tiled_ok(L0);
     if (c->opt.precision == 1) {
       if (zs && c->tail32 != 0) {
@@ -874,7 +877,7 @@ static hipError_t cycle_body(sbm_ctx *c, const double *f, int mode) {
       // and scale it themselves (the FP64 z is never written)
       return launch_store_sqrt(c->scal, c->scal + 6, c->st);
     }
-    if ((L0.g.hx && skip && c->tail64 != 0) || leg2_ok(c, 0)) {
+    if (((L0.g.hx || zs) && skip && c->tail64 != 0) || leg2_ok(c, 0)) {
       c->zero_start = true;
     } else if (skip && c->tail64 != 0) {
       if ((e = launch_zero_sweep<double>(L0, L0.psi64, L0.c64, c->kr, L0.t, opt_omega(c->opt), 0,
