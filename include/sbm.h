@@ -143,7 +143,9 @@ void sbm_default_options(sbm_options *opts);
 int sbm_num_levels(const sbm_grid *grid);
 
 /* Device workspace bytes needed by sbm_create for this grid (FP64 and FP32
- * hierarchies, residual partial sums, bottom scratch).  0 on invalid input. */
+ * hierarchies, residual partial sums, bottom scratch; the bottom's inverse, at
+ * most 18.9 MB, only where the options use it: a context created without it
+ * keeps the bottom CG if such options are set later).  0 on invalid input. */
 size_t sbm_workspace_bytes(const sbm_grid *grid, const sbm_options *opts);
 
 /* Creates a context.  workspace: device pointer, 256-byte aligned, at least

@@ -32,10 +32,10 @@ struct Level {
   Coef<float> c32;
   double *psi64 = nullptr;
   float *psi32 = nullptr;
-  // FP64 vectors: level 0 uses f (load), r (residual / ping-pong); coarse
-  // levels use e (correction), f (restricted residual), t (ping-pong / residual)
+  // FP64 vectors: level 0 uses f (load), t (residual / ping-pong), e (the load of a
+  // solve in its rows, where that is not f); coarse levels use e (correction), f
+  // (restricted residual), t (ping-pong / residual)
   double *e = nullptr, *f = nullptr, *t = nullptr;
-  double *fs = nullptr;  // finest level: the load in split rows
   int hx64 = 0, hx32 = 0;  // g.hx while a solve with FP64 / FP32 cycles runs
   // FP32 vectors of the mixed cycle
   float *e32 = nullptr, *f32 = nullptr, *t32 = nullptr;

@@ -77,7 +77,7 @@ struct sbm_ctx {
   DispValues zero_dv{};
   double fnorm = 0.0;
   int last_bottom_iters = 0;
-  bool fs_ok = false;  // L[0].fs holds the current load
+  bool split_load = false;  // L[0].e holds the problem's load in split rows
   double *x0 = nullptr;  // finest-level iterate (fixed address for captured cycles)
   double *kr = nullptr, *kz = nullptr, *kp = nullptr, *kq = nullptr;  // flexible CG vectors
   // set while a CG preconditioner cycle is built: its last finest half-sweep
@@ -275,6 +275,15 @@ struct Carver {
   }
 };
 
+// Options with which FP64 cycles may apply the bottom's inverse: bottom_rtol is near its
+// default 1e-12 and the iterations are not capped.
+static bool inverse_opts(const sbm_options &o) {
+  return o.precision == 0 && o.bottom_max_iter <= 0 && o.bottom_rtol >= 1e-13 &&
+         o.bottom_rtol <= 1e-12;
+}
+
+// The memory of a context.  The bottom's inverse (at most 18.9 MB) only where the options
+// at creation can use it.
 static size_t carve(sbm_ctx *c, char *base) {
   Carver cv{base};
   const int d = c->dim;
@@ -295,7 +304,6 @@ static size_t carve(sbm_ctx *c, char *base) {
     L.e32 = cv.take<float>(nv);
     L.f32 = cv.take<float>(nv);
     L.t32 = cv.take<float>(nv);
-    if (l == 0 && L.hx64) L.fs = cv.take<double>(nv);
     maxblocks = std::max<int64_t>(maxblocks, grid_blocks(L.g.nn));
     maxblocks = std::max<int64_t>(maxblocks, num_blocks(L.g.nc));
   }
@@ -318,7 +326,7 @@ static size_t carve(sbm_ctx *c, char *base) {
   c->b_r64 = cv.take<double>(nb);
   c->tail_args = cv.take<char>(2 * (int64_t)kTailArgBytes);
   c->tail_A = cv.take<double>((int64_t)(kTailDenseBytes / sizeof(double)));
-  c->tail_inv = cv.take<double>(B.g.nn <= kInverseNodes ? nb * nb : 0);
+  c->tail_inv = B.g.nn <= kInverseNodes && inverse_opts(c->opt) ? cv.take<double>(nb * nb) : nullptr;
   return cv.off + 256;
 }
 
@@ -619,17 +627,15 @@ static hipError_t bottom32(sbm_ctx *c, const float *f, float *x) {
                              c->opt.bottom_rtol, bottom_maxit(c), c->iflag + 4, c->st);
 }
 
-// Whether FP64 cycles may apply the bottom's inverse: the bottom is a coarse level
-// (its iterate starts from zero) of at most kInverseNodes nodes, bottom_rtol is
-// near its default 1e-12 and the iterations are not capped.  Its columns are
-// solved until the CG's updated residual is 1e-2 bottom_rtol; each product is kept
-// only if its own residual is that of a solve, else the CG runs (bottom_solved).  A
-// looser CG is cheaper and stays.
+// Whether FP64 cycles may apply the bottom's inverse: the options allow it and did at
+// creation, the bottom is a coarse level (its iterate starts from zero) of at most
+// kInverseNodes nodes.  The columns are solved until the CG's updated residual is 1e-2
+// bottom_rtol; each product is kept only if its own residual is that of a solve, else
+// the CG runs (bottom_solved).  A looser CG is cheaper and stays.
 static bool inverse_ok(const sbm_ctx *c) {
   const Level &B = c->L.back();
-  return c->nlev > 1 && B.g.nn <= kInverseNodes &&
-         (c->tail64 < 0 || c->dim * B.g.nn <= kTailInverse) && c->opt.bottom_max_iter <= 0 &&
-         c->opt.bottom_rtol >= 1e-13 && c->opt.bottom_rtol <= 1e-12;
+  return c->tail_inv && inverse_opts(c->opt) && c->nlev > 1 &&
+         (c->tail64 < 0 || c->dim * B.g.nn <= kTailInverse);
 }
 
 // Cycles of a solve before its inverse is formed (once per problem, as many CG solves
@@ -644,7 +650,7 @@ static int cycles_before_inverse(const sbm_ctx *c) {
 
 // Before cycle m (0 the first) of a solve: switches the inverse on or off.
 static hipError_t prepare_inverse(sbm_ctx *c, int m) {
-  if (c->opt.precision != 0 || !inverse_ok(c)) return hipSuccess;
+  if (!inverse_ok(c)) return hipSuccess;
   const bool on = m >= cycles_before_inverse(c);
   hipError_t e;
   if (on && !c->inv_ready) {
@@ -1228,6 +1234,7 @@ size_t sbm_workspace_bytes(const sbm_grid *grid, const sbm_options *opts) {
   sbm_ctx c;
   c.dim = grid->dim;
   c.nlev = count_levels(grid);
+  c.opt = *opts;
   level_shapes(grid, c.nlev, c.L);
   return carve(&c, nullptr);
 }
@@ -1243,6 +1250,7 @@ sbm_status sbm_create(const sbm_grid *grid, const sbm_options *opts, void *works
   sbm_ctx *c = new sbm_ctx();
   c->dim = grid->dim;
   c->nlev = count_levels(grid);
+  c->opt = *opts;
   level_shapes(grid, c->nlev, c->L);
   const size_t need = carve(c, nullptr);
   if (workspace_bytes < need) {
@@ -1252,7 +1260,6 @@ sbm_status sbm_create(const sbm_grid *grid, const sbm_options *opts, void *works
   c->ws = (char *)workspace;
   c->ws_bytes = workspace_bytes;
   carve(c, c->ws);
-  c->opt = *opts;
   c->st = (hipStream_t)hip_stream;
   {
     int dev = 0, lds = 0;
@@ -1478,7 +1485,7 @@ static sbm_status set_problem_impl(sbm_ctx *c, const double *psi_raw, int cube,
   HIP_TRY(hipStreamSynchronize(c->st));
   memcpy(&flags, c->host, sizeof(int));
   c->have_problem = false;
-  c->fs_ok = false;
+  c->split_load = false;
   if (flags & 1) return fail(SBM_E_NONFINITE, "NaN/Inf in psi or body force");
   if (flags & 2) return fail(SBM_E_DIAG, "a free DOF has no solid cell around it (zero diagonal)");
   // fnorm = ||fA - K uD|| over free DOF (uD: prescribed values, 0 elsewhere)
@@ -1517,11 +1524,11 @@ sbm_status sbm_solve(sbm_ctx *c, double *u, double *hist, int cap, int *ncyc, do
   HIP_TRY(launch_set_dirichlet(L0, u, c->dv, c->st));
   const RowsScope rows(c);
   if (!L0.g.hx) return solve_impl(c, L0.f, c->fnorm, u, hist, cap, ncyc, final_rel);
-  if (!c->fs_ok) {  // the load in the solve's rows, once per problem
-    HIP_TRY(launch_to_split<double>(L0, L0.f, L0.fs, c->st));
-    c->fs_ok = true;
+  if (!c->split_load) {  // the load in the solve's rows, until another takes the place
+    HIP_TRY(launch_to_split<double>(L0, L0.f, L0.e, c->st));
+    c->split_load = true;
   }
-  return solve_impl(c, L0.fs, c->fnorm, u, hist, cap, ncyc, final_rel);
+  return solve_impl(c, L0.e, c->fnorm, u, hist, cap, ncyc, final_rel);
 }
 
 sbm_status sbm_solve_rhs(sbm_ctx *c, const double *g, double *x, double *hist, int cap, int *ncyc,
@@ -1532,6 +1539,7 @@ sbm_status sbm_solve_rhs(sbm_ctx *c, const double *g, double *x, double *hist, i
   HIP_TRY(launch_set_dirichlet(L0, x, c->zero_dv, c->st));
   const RowsScope rows(c);
   // g on the free DOF in the solve's rows, and its norm
+  c->split_load = false;
   HIP_TRY(launch_take_load(L0, g, L0.e, c->partials, c->st));
   HIP_TRY(launch_finalize_sum(c->partials, num_blocks(L0.g.nn), c->scal, c->st));
   HIP_TRY(hipMemcpyAsync(c->host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->st));

@@ -1,6 +1,7 @@
 """Solves of one problem, one after another and after the options changed and came back,
 are the same bits: how the bottom is solved depends on the cycle, not on what ran before.
-Bottoms inside the tail and outside it, V-cycles and CG, the adjoint entry in between."""
+Bottoms inside the tail and outside it, split rows, V-cycles and CG, the adjoint entry (whose
+load takes the place of the problem's in split rows) in between."""
 import numpy as np
 import pytest
 
@@ -10,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("krylov", [0, 1])
-@pytest.mark.parametrize("ncell", [(16, 16, 16), (28, 28, 28), (56, 40, 48), (64, 48)])
+@pytest.mark.parametrize("ncell", [(16, 16, 16), (28, 28, 28), (56, 40, 48), (64, 48),
+                                   (128, 32, 16)])
 def test_same_bits(ncell, krylov):
     from paper_2212_02362_amd import Solver
     say("repeated solves", ncell, krylov)
