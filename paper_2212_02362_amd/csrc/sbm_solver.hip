@@ -819,7 +819,8 @@ static sbm_status residual_norm2_keep(sbm_ctx *c, const double *u, const double 
 // As residual_norm2 on a tiled finest level, the residual written as the FP32
 // cycle's load fp32((f - K u) / s), s^2 = scal[8]: the norm of the residual
 // before (the lifted load's at first).  The cycle is linear in its load, so any
-// positive scale near its size does; this one is known before the pass.
+// positive scale near its size does; this one is known before the pass (and the
+// loop casts again where it turns out far off).
 static sbm_status residual_norm2_cast(sbm_ctx *c, const double *u, const double *f,
                                       double *out) {
   Level &L = c->L[0];
@@ -1151,7 +1152,8 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
   const bool keep = c->opt.precision == 1 && residual_sweep_ok(L0);
   // mixed on a tiled finest level: the convergence test casts
   const bool cast = c->opt.precision == 1 && !keep;
-  if (cast) HIP_TRY(launch_fill<double>(c->scal + 8, 1, fnorm * fnorm, c->st));
+  double cast_ss = fnorm * fnorm;  // scal[8]
+  if (cast) HIP_TRY(launch_fill<double>(c->scal + 8, 1, cast_ss, c->st));
   const bool keep_sweep = keep && c->opt.smoother == 0 && c->opt.nu_pre >= 1 && c->nlev > 1 &&
                           c->tail32 != 0;
   for (m = 0;; ++m) {
@@ -1181,6 +1183,16 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
       g_last_error = "max_cycles reached";
       status = SBM_NOT_CONVERGED;
       break;
+    }
+    if (cast) {
+      // Scaled by a norm more than 2^20 off its own (a start far from the solution, or
+      // very near it), the load would leave FP32's range with the units of the problem:
+      // cast again.
+      if (!(ss <= 0x1p40 * cast_ss && ss >= 0x1p-40 * cast_ss)) {
+        HIP_TRY(launch_fill<double>(c->scal + 8, 1, ss, c->st));
+        HIP_TRY(launch_residual_cast(L0, c->x0, f, L0.f32, c->scal + 8, c->partials, c->st));
+      }
+      cast_ss = ss;  // the cycle leaves it in scal[8]
     }
     HIP_TRY(prepare_inverse(c, m));
     s = run_cycle(c, f, keep_sweep ? 3 : cast ? 5 : (fused || keep ? 2 : 0));
