@@ -1800,12 +1800,13 @@ sbm_status sbm_amr_solve(sbm_amr_ctx *c, double *const *u, double *hist_host, in
     r[a] = c->lv[a].r;
   }
   AMR_TRY(amr_inject_all(c, u));
-  double rho = 0.0, rho_min = INFINITY;
+  double rho = 0.0, before = 0.0, rho_min = INFINITY;
   sbm_status status = SBM_NOT_CONVERGED;
   int m = 0;
   for (m = 0;; ++m) {
     AMR_TRY(amr_comp_residual(c, u, f, r, true));
     const double ss = c->host[0];
+    before = rho;
     rho = c->fnorm > 0.0 ? sqrt(ss) / c->fnorm : (ss > 0.0 ? INFINITY : 0.0);
     if (hist_host && m < hist_cap) hist_host[m] = rho;
     if (!isfinite(rho)) {
@@ -1856,7 +1857,8 @@ sbm_status sbm_amr_solve(sbm_amr_ctx *c, double *const *u, double *hist_host, in
                                      a >= 1 ? c->lv[a].unknown_tiles() : nullptr));
     } else {
       for (int a = 0; a <= A; ++a) AMR_HIP(amr_zero<double>(c, c->lv[a], c->lv[a].e));
-      AMR_HIP(base_prepare(c->base, m));
+      AMR_HIP(base_prepare(c->base, m,
+                           cycles_left(rho, before, c->opt.rtol, m, c->opt.max_cycles)));
       AMR_HIP(amr_fas<double>(c, A));
       for (int a = 0; a <= A; ++a)
         AMR_HIP(launch_update<double>(c->lv[a].L, a >= 1 ? c->lv[a].cls : nullptr, u[a],

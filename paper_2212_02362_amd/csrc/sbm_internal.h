@@ -355,7 +355,11 @@ void set_coefs(Level &L, double lam, double mu, int dim);
 // One V-cycle of the uniform hierarchy of c from its finest level: x (in/out)
 // and f are finest-level vectors in FP64 (precision 0) or FP32 (precision 1).
 hipError_t base_vcycle(sbm_ctx *c, int precision, void *x, const void *f);
-// Before cycle m of a composite solve in FP64: what its FP64 cycles use besides the problem.
-hipError_t base_prepare(sbm_ctx *c, int m);
+// Cycles from residual rho (before it: `before`) to rtol at the last one's rate, at most
+// max_cycles - m.
+double cycles_left(double rho, double before, double rtol, int m, int max_cycles);
+// Before cycle m of a composite solve in FP64 with about `left` more to make: what its
+// cycles use besides the problem.
+hipError_t base_prepare(sbm_ctx *c, int m, double left);
 
 }  // namespace sbm

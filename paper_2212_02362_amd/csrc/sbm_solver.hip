@@ -638,20 +638,26 @@ static bool inverse_ok(const sbm_ctx *c) {
          (c->tail64 < 0 || c->dim * B.g.nn <= kTailInverse);
 }
 
-// Cycles of a solve before its inverse is formed (once per problem, as many CG solves
-// as DOF side by side) and used: as many as it costs, so a solve of few cycles pays
-// for none and one that goes on pays at most twice its CGs.  Up to 512 DOF forming
-// takes little more than one CG (112 nodes: 247 against 215 us); larger bottoms take a
-// few (512 nodes: 1530 against 420 us).  The rule looks at the cycle alone, not at
-// whether an earlier solve has formed it: repeated solves make the same steps.
-static int cycles_before_inverse(const sbm_ctx *c) {
-  return c->dim * c->L.back().g.nn <= kTailInverse ? 1 : 4;
+// Cycles that a solve has to have left for the inverse to pay.  Forming it is as many CG
+// solves as DOF side by side: up to 512 DOF little more than one CG (112 nodes: 247
+// against 215 us), above a few (28^3 cells, 512 nodes: 2.8 ms against 0.63 ms per cycle).
+static int inverse_pays(const sbm_ctx *c) {
+  return c->dim * c->L.back().g.nn <= kTailInverse ? 2 : 6;
 }
 
-// Before cycle m (0 the first) of a solve: switches the inverse on or off.
-static hipError_t prepare_inverse(sbm_ctx *c, int m) {
+double sbm::cycles_left(double rho, double before, double rtol, int m, int max_cycles) {
+  const double cap = max_cycles - m;
+  if (!(rho > rtol && rho < before && rtol > 0.0)) return cap;
+  return std::min(cap, ceil(log(rtol / rho) / log(rho / before)));
+}
+
+// Before cycle m (0 the first) of a solve that has about `left` more to make: switches
+// the bottom from the CG to its inverse.  The first cycle, which knows no rate, keeps the
+// CG.  The rule looks at this solve alone, not at whether an earlier one has formed the
+// inverse: repeated solves make the same steps.
+static hipError_t prepare_inverse(sbm_ctx *c, int m, double left) {
   if (!inverse_ok(c)) return hipSuccess;
-  const bool on = m >= cycles_before_inverse(c);
+  const bool on = m > 0 && (c->inv_on || left >= inverse_pays(c));
   hipError_t e;
   if (on && !c->inv_ready) {
     if ((e = launch_bottom_inverse(c->L.back(), c->tail_inv, c->iflag + 13,
@@ -665,7 +671,7 @@ static hipError_t prepare_inverse(sbm_ctx *c, int m) {
   return launch_fill<int>(c->iflag + 13, 1, on ? 1 : 0, c->st);
 }
 
-hipError_t sbm::base_prepare(sbm_ctx *c, int m) { return prepare_inverse(c, m); }
+hipError_t sbm::base_prepare(sbm_ctx *c, int m, double left) { return prepare_inverse(c, m, left); }
 
 // Whether level l runs its legs of a FP64 V-cycle in one launch each: 2D, one or two
 // sweeps on either leg (the halo of more would outgrow the tile), above the tail,
@@ -1027,7 +1033,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
   const bool rzf = rz_fused(c);
   const bool castf = cast_fused(c);
   const int nrz = !rzf ? 0 : c->opt.precision == 1 ? rb_tiled_partials(L0) : rb_split_partials(L0);
-  double rho_min = INFINITY, rho = 0.0;
+  double rho_min = INFINITY, rho = 0.0, before = 0.0;
   sbm_status status = SBM_NOT_CONVERGED;
   // the preconditioned residual: kz, or (mixed) scal[6] * the FP32 correction
   const ZSrc z = c->opt.precision == 1 ? ZSrc{nullptr, L0.e32, c->scal + 6}
@@ -1062,7 +1068,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
       break;
     }
     if (restart) {
-      HIP_TRY(prepare_inverse(c, m));
+      HIP_TRY(prepare_inverse(c, m, 0.0));
       SBM_TRY(run_cycle(c, nullptr, 1));
       if (rzf) {
         HIP_TRY(launch_finalize_sum(c->partials, nrz, c->scal + prev, c->st));
@@ -1093,6 +1099,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
       break;
     }
     ++m;
+    before = rho;
     rho = fnorm > 0.0 ? sqrt(c->host[0]) / fnorm : 0.0;
     if (rho <= c->opt.rtol) {
       // accept on the true residual only; otherwise restart from it
@@ -1109,7 +1116,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
       continue;
     }
     if (hist && m < cap) hist[m] = rho;
-    HIP_TRY(prepare_inverse(c, m + 1));
+    HIP_TRY(prepare_inverse(c, m, cycles_left(rho, before, c->opt.rtol, m, c->opt.max_cycles)));
     SBM_TRY(run_cycle(c, nullptr, castf ? 4 : 1));
     if (rzf) {
       HIP_TRY(launch_finalize_sum(c->partials, nrz, c->scal + next, c->st));
@@ -1136,7 +1143,7 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
                              int cap, int *ncyc, double *final_rel) {
   if (c->opt.krylov == 1) return solve_krylov(c, f, fnorm, u, hist, cap, ncyc, final_rel);
   Level &L0 = c->L[0];
-  double rho_min = INFINITY, rho = 0.0;
+  double rho_min = INFINITY, rho = 0.0, before = 0.0;
   int m = 0;
   sbm_status status = SBM_NOT_CONVERGED;
   HIP_TRY(launch_to_split<double>(L0, u, c->x0, c->st));
@@ -1163,6 +1170,7 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
                    : cast ? residual_norm2_cast(c, c->x0, f, &ss)
                           : residual_norm2(c, c->x0, f, &ss);
     if (s != SBM_OK) return s;
+    before = rho;
     rho = fnorm > 0.0 ? sqrt(ss) / fnorm : (ss > 0.0 ? INFINITY : 0.0);
     if (hist && m < cap) hist[m] = rho;
     if (!isfinite(rho)) {
@@ -1194,7 +1202,7 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
       }
       cast_ss = ss;  // the cycle leaves it in scal[8]
     }
-    HIP_TRY(prepare_inverse(c, m));
+    HIP_TRY(prepare_inverse(c, m, cycles_left(rho, before, c->opt.rtol, m, c->opt.max_cycles)));
     s = run_cycle(c, f, keep_sweep ? 3 : cast ? 5 : (fused || keep ? 2 : 0));
     if (s != SBM_OK) return s;
   }

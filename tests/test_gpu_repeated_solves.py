@@ -33,3 +33,24 @@ def test_same_bits(ncell, krylov):
         assert np.array_equal(to_np(u), to_np(v)), change
         y, hist_y, _ = S.solve_rhs(fB)
         assert np.array_equal(hist_x, hist_y) and np.array_equal(to_np(x), to_np(y)), change
+
+
+@pytest.mark.parametrize("krylov", [0, 1])
+@pytest.mark.parametrize("ncell,cycles", [((16, 16, 16), 1), ((16, 16, 16), 2), ((64, 48), 2),
+                                          ((28, 28, 28), 6)])
+def test_few_cycles_keep_the_cg(ncell, cycles, krylov):
+    """Solves too short to earn back the bottom's inverse: the bits of the bottom CG (kept
+    by a cap on its iterations that is never reached)."""
+    from paper_2212_02362_amd import Solver
+    say("few cycles", ncell, cycles, krylov)
+    p = random_problem(ncell, seed=6, floor=1e-2, cubic=True)
+    S = Solver(p.ncell, p.h, rtol=0.0, max_cycles=cycles, krylov=krylov)
+    got = []
+    for cap in (0, 100000):
+        S.set_options(bottom_max_iter=cap)
+        S.set_problem_from(p)
+        for _ in range(2):
+            u, hist, _ = S.solve()
+            got.append((to_np(u), hist))
+    for u, hist in got[1:]:
+        assert np.array_equal(u, got[0][0]) and np.array_equal(hist, got[0][1])
