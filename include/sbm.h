@@ -342,9 +342,12 @@ sbm_status sbm_compliance(sbm_ctx *ctx, const double *u, double *J_host);
  * Cycles then run launch by launch (use_graphs is ignored while enabled).
  * sbm_profile(ctx, 1) enables and clears, sbm_profile(ctx, 0) disables.
  * sbm_profile_read fills ms_host[SBM_PROF_N] (total milliseconds) and
- * count_host[SBM_PROF_N] (launches) per class. */
+ * count_host[SBM_PROF_N] (launches) per class.  A launch that does the work of
+ * several classes counts once: 2D FP64 Gauss-Seidel cycles of one or two sweeps
+ * per leg (fused_sweep 0) run each leg in one launch, which SMOOTH counts with
+ * its residual and restriction, or prolongation, in it (those read 0). */
 typedef enum {
-  SBM_PROF_SMOOTH = 0,   /* smoother sweep / half-sweep on the finest level */
+  SBM_PROF_SMOOTH = 0,   /* smoother sweep / half-sweep / 2D leg on the finest level */
   SBM_PROF_RESIDUAL = 1, /* residual feeding the restriction, finest level */
   SBM_PROF_RESTRICT = 2, /* restriction from the finest level */
   SBM_PROF_PROLONG = 3,  /* prolongation-add into the finest level */

@@ -251,10 +251,10 @@ __device__ __forceinline__ void stencil2(const CO &C, const T (&P)[2][2], UF &&U
 // Neighbour offsets are clamped at the box boundary: every term that would
 // reach outside carries a zero psi weight, so the clamped value never counts.
 // uo (optional, 3D): the buffer of the other colour's nodes (the six face
-// neighbours); u then holds the node's own colour, and is finite everywhere.  ctr (optional) receives u at
-// the node itself.  GATHER keeps every load
-// ahead of the arithmetic (a scheduling barrier); without it the compiler may
-// interleave them, which needs fewer registers.
+// neighbours); u then holds the node's own colour, and is finite everywhere.  ctr
+// (optional) receives u at the node itself.  GATHER keeps every load ahead of the
+// arithmetic (a scheduling barrier); without it the compiler may interleave them,
+// which needs fewer registers.
 template <typename T, int DIM, bool GATHER = true, typename G = Geom, typename CO = Coef<T>>
 __device__ __forceinline__ void node_stencil(const G &g, const CO &C,
                                              const T *__restrict__ psi,

@@ -69,7 +69,7 @@ __device__ __forceinline__ void jacobi_eigs3(double a[3][3], double e[3]) {
 
 // H is read and max(H, W0+) written to Hn; in place (Hn = H) only where it
 // grows.  Bound by memory: 33 B per cell in 2D (4096^2 cells: 120 us, 4.6 TB/s; a copy of
-// H and an update in place 104 + 51 us).
+// H and an update in place 51 + 104 us).
 template <int DIM>
 __global__ __launch_bounds__(kBlock) void k_crack_drive(Geom g, double lam, double mu, double ihx,
                                                        double ihy, double ihz,

@@ -153,10 +153,8 @@ hipError_t launch_rb_split(const Level &L, const T *psi, const Coef<T> &C, const
 int rb_split_partials(const Level &L);
 // Node vectors between natural rows and the level's (a copy where it has
 // natural rows).
-template <typename T>
-hipError_t launch_to_split(const Level &L, const T *src, T *dst, hipStream_t st);
-template <typename T>
-hipError_t launch_from_split(const Level &L, const T *src, T *dst, hipStream_t st);
+hipError_t launch_to_split(const Level &L, const double *src, double *dst, hipStream_t st);
+hipError_t launch_from_split(const Level &L, const double *src, double *dst, hipStream_t st);
 // A load given in natural rows, 0 on displacement DOF, in the level's rows, and
 // num_blocks(nn) partial sums of its squares.
 hipError_t launch_take_load(const Level &L, const double *f, double *out, double *partials,
@@ -243,7 +241,7 @@ hipError_t launch_axpy_free(const Level &L, double *x, const double *p, const do
 hipError_t launch_scale_cast(const double *r, float *r32, int64_t n, const double *ss,
                              hipStream_t st);
 // The first colour half-sweep from a zero iterate for the load f into t (split
-// rows: the relaxed colour alone, else zeros at the other nodes).
+// rows: the relaxed colour alone; else, FP64, zeros at the other nodes).
 template <typename T>
 hipError_t launch_zero_sweep(const Level &L, const T *psi, const Coef<T> &C, const T *f, T *t,
                              double omega, int colour, hipStream_t st);

@@ -693,10 +693,10 @@ __global__ __launch_bounds__(kBlock) void k_take_load(Geom g, int hs, const doub
 }
 
 // A node vector between natural and split rows (to_split: from natural).
-template <typename T, bool TO_SPLIT>
+template <bool TO_SPLIT>
 __global__ __launch_bounds__(kBlock) void k_relayout(Geom g, int comps, int hs,
-                                                     const T *__restrict__ src,
-                                                     T *__restrict__ dst) {
+                                                     const double *__restrict__ src,
+                                                     double *__restrict__ dst) {
   const int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (id >= g.nn) return;
   int i, j, k;
@@ -1662,16 +1662,13 @@ hipError_t launch_take_load(const Level &L, const double *f, double *out, double
   SBM_LAUNCH((k_take_load<2>), num_blocks(L.g.nn), kBlock, st, L.g, L.g.hx, f, out, partials);
 }
 
-template <typename T>
-hipError_t launch_to_split(const Level &L, const T *src, T *dst, hipStream_t st) {
-  if (!L.g.hx) return launch_copy<T>(src, dst, (int64_t)L.g.dim * L.g.nn, st);
-  SBM_LAUNCH((k_relayout<T, true>), num_blocks(L.g.nn), kBlock, st, L.g, L.g.dim, L.g.hx, src, dst);
+hipError_t launch_to_split(const Level &L, const double *src, double *dst, hipStream_t st) {
+  if (!L.g.hx) return launch_copy<double>(src, dst, (int64_t)L.g.dim * L.g.nn, st);
+  SBM_LAUNCH((k_relayout<true>), num_blocks(L.g.nn), kBlock, st, L.g, L.g.dim, L.g.hx, src, dst);
 }
-template <typename T>
-hipError_t launch_from_split(const Level &L, const T *src, T *dst, hipStream_t st) {
-  if (!L.g.hx) return launch_copy<T>(src, dst, (int64_t)L.g.dim * L.g.nn, st);
-  SBM_LAUNCH((k_relayout<T, false>), num_blocks(L.g.nn), kBlock, st, L.g, L.g.dim, L.g.hx, src,
-             dst);
+hipError_t launch_from_split(const Level &L, const double *src, double *dst, hipStream_t st) {
+  if (!L.g.hx) return launch_copy<double>(src, dst, (int64_t)L.g.dim * L.g.nn, st);
+  SBM_LAUNCH((k_relayout<false>), num_blocks(L.g.nn), kBlock, st, L.g, L.g.dim, L.g.hx, src, dst);
 }
 
 hipError_t launch_check_diag(const Level &L, int *flag, hipStream_t st) {
@@ -1710,9 +1707,11 @@ hipError_t launch_cg_update_r(const Level &L, double *r, const double *q, const 
                               double *pz, hipStream_t st, float *r32, const double *ss) {
   if (L.g.dim == 3)
     return by_rows(L.g, [&](const auto &g) {
-      SBM_LAUNCH((k_cg_update_r<3, SBM_ROWS(g)>), num_blocks(L.g.nn), kBlock, st, g, r, q, z, rz, pq, alpha_out, pr, pz, r32, ss);
+      SBM_LAUNCH((k_cg_update_r<3, SBM_ROWS(g)>), num_blocks(L.g.nn), kBlock, st, g, r, q, z, rz,
+                 pq, alpha_out, pr, pz, r32, ss);
     });
-  SBM_LAUNCH((k_cg_update_r<2, Geom>), num_blocks(L.g.nn), kBlock, st, L.g, r, q, z, rz, pq, alpha_out, pr, pz, r32, ss);
+  SBM_LAUNCH((k_cg_update_r<2, Geom>), num_blocks(L.g.nn), kBlock, st, L.g, r, q, z, rz, pq,
+             alpha_out, pr, pz, r32, ss);
 }
 
 hipError_t launch_xpby_x(const Level &L, double *x, double *p, const ZSrc &z,
@@ -1720,9 +1719,11 @@ hipError_t launch_xpby_x(const Level &L, double *x, double *p, const ZSrc &z,
                          const double *alpha, hipStream_t st) {
   if (L.g.dim == 3)
     return by_rows(L.g, [&](const auto &g) {
-      SBM_LAUNCH((k_xpby_x<3, SBM_ROWS(g)>), num_blocks(L.g.nn), kBlock, st, g, x, p, z, rznew, rzold, rz, alpha);
+      SBM_LAUNCH((k_xpby_x<3, SBM_ROWS(g)>), num_blocks(L.g.nn), kBlock, st, g, x, p, z, rznew,
+                 rzold, rz, alpha);
     });
-  SBM_LAUNCH((k_xpby_x<2, Geom>), num_blocks(L.g.nn), kBlock, st, L.g, x, p, z, rznew, rzold, rz, alpha);
+  SBM_LAUNCH((k_xpby_x<2, Geom>), num_blocks(L.g.nn), kBlock, st, L.g, x, p, z, rznew, rzold, rz,
+             alpha);
 }
 
 hipError_t launch_axpy_free(const Level &L, double *x, const double *p, const double *alpha,
@@ -1803,11 +1804,14 @@ hipError_t launch_zero_sweep(const Level &L, const T *psi, const Coef<T> &C, con
   if (L.g.hx)
     SBM_LAUNCH((k_zero_split<T>), grid_blocks((int64_t)L.g.hx * L.g.ny * L.g.nz), kBlock, st, L.g, C,
                psi, f, t, (T)omega, colour);
-  if (L.g.dim == 3)
-    SBM_LAUNCH((k_zero_sweep<T, 3>), grid_blocks(L.g.nn), kBlock, st, L.g, C, psi, f, t, (T)omega,
+  if constexpr (sizeof(T) == 8) {
+    if (L.g.dim == 3)
+      SBM_LAUNCH((k_zero_sweep<T, 3>), grid_blocks(L.g.nn), kBlock, st, L.g, C, psi, f, t, omega,
+                 colour);
+    SBM_LAUNCH((k_zero_sweep<T, 2>), grid_blocks(L.g.nn), kBlock, st, L.g, C, psi, f, t, omega,
                colour);
-  SBM_LAUNCH((k_zero_sweep<T, 2>), grid_blocks(L.g.nn), kBlock, st, L.g, C, psi, f, t, (T)omega,
-             colour);
+  }
+  return hipErrorInvalidValue;  // FP32: split rows only
 }
 
 hipError_t launch_scale_cast_sweep(const Level &L, const double *r, float *r32, float *t32,
@@ -1970,8 +1974,6 @@ hipError_t launch_sensitivity(const Level &L, double lam, double mu, const Tract
   template hipError_t launch_fill<T>(T *, int64_t, T, hipStream_t);                             \
   template hipError_t launch_zero_sweep<T>(const Level &, const T *, const Coef<T> &, const T *, \
                                            T *, double, int, hipStream_t);                      \
-  template hipError_t launch_to_split<T>(const Level &, const T *, T *, hipStream_t);           \
-  template hipError_t launch_from_split<T>(const Level &, const T *, T *, hipStream_t);         \
   template hipError_t launch_copy<T>(const T *, T *, int64_t, hipStream_t);                     \
   template hipError_t launch_bottom_cg<T>(const Level &, const T *, const Coef<T> &, const T *, \
                                           T *, T *, T *, T *, double, int, int *, hipStream_t, \

@@ -118,8 +118,8 @@ __global__ __launch_bounds__(kBlock) void k_plastic_source(Geom g, double lam, d
 // Radial return (linear combined hardening) of every cell for the strain of
 // u: one thread per cell.  The state is read from (ep, alpha, beta) and written
 // to (epn, alphan, betan); in place (the same arrays) only where the cell yields.
-// Bound by memory: 232 B per cell out of place (128^3: 108 us, 4.5 TB/s; a copy of
-// the state and an update in place 109 + 84 us).
+// Bound by memory: 232 B per cell out of place (128^3: 108 us, 4.5 TB/s; copies of
+// the state and an update in place 84 + 109 us).
 // Counts the yielding cells (integer sum per block, one atomic per block).
 __global__ __launch_bounds__(kBlock) void k_return_map(Geom g, double mu, double sy, double hb,
                                                       double theta, double ihx, double ihy,

@@ -1038,7 +1038,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
   // the preconditioned residual: kz, or (mixed) scal[6] * the FP32 correction
   const ZSrc z = c->opt.precision == 1 ? ZSrc{nullptr, L0.e32, c->scal + 6}
                                        : ZSrc{c->kz, nullptr, nullptr};
-  HIP_TRY(launch_to_split<double>(L0, u, c->x0, c->st));
+  HIP_TRY(launch_to_split(L0, u, c->x0, c->st));
   {
     ProfScope ps(c, SBM_PROF_NORM, true);
     HIP_TRY((launch_residual<double>(L0, L0.psi64, L0.c64, c->x0, f, c->kr, c->partials, c->st)));
@@ -1130,7 +1130,7 @@ static sbm_status solve_krylov(sbm_ctx *c, const double *f, double fnorm, double
   }
   if (ncyc) *ncyc = m;
   if (final_rel) *final_rel = rho;
-  HIP_TRY(launch_from_split<double>(L0, c->x0, u, c->st));
+  HIP_TRY(launch_from_split(L0, c->x0, u, c->st));
   HIP_TRY(hipStreamSynchronize(c->st));
   if (c->prof_on) prof_harvest(c);
   return status;
@@ -1146,7 +1146,7 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
   double rho_min = INFINITY, rho = 0.0, before = 0.0;
   int m = 0;
   sbm_status status = SBM_NOT_CONVERGED;
-  HIP_TRY(launch_to_split<double>(L0, u, c->x0, c->st));
+  HIP_TRY(launch_to_split(L0, u, c->x0, c->st));
   // FP64 V-cycles with Gauss-Seidel pre-smoothing: the convergence test also
   // makes the next cycle's first half-sweep (the iterate itself is left as it is, so a
   // converged solve returns the tested iterate)
@@ -1208,7 +1208,7 @@ static sbm_status solve_impl(sbm_ctx *c, const double *f, double fnorm, double *
   }
   if (ncyc) *ncyc = m;
   if (final_rel) *final_rel = rho;
-  HIP_TRY(launch_from_split<double>(L0, c->x0, u, c->st));
+  HIP_TRY(launch_from_split(L0, c->x0, u, c->st));
   HIP_TRY(hipStreamSynchronize(c->st));
   if (c->prof_on) prof_harvest(c);
   return status;
@@ -1545,7 +1545,7 @@ sbm_status sbm_solve(sbm_ctx *c, double *u, double *hist, int cap, int *ncyc, do
   const RowsScope rows(c);
   if (!L0.g.hx) return solve_impl(c, L0.f, c->fnorm, u, hist, cap, ncyc, final_rel);
   if (!c->split_load) {  // the load in the solve's rows, until another takes the place
-    HIP_TRY(launch_to_split<double>(L0, L0.f, L0.e, c->st));
+    HIP_TRY(launch_to_split(L0, L0.f, L0.e, c->st));
     c->split_load = true;
   }
   return solve_impl(c, L0.e, c->fnorm, u, hist, cap, ncyc, final_rel);

@@ -9,7 +9,7 @@
 // read the old ones).  The result goes to another buffer than the one read.  Bound by
 // latency: one round trip for everything the tile reads, then two stencils.  A sweep,
 // two half-sweeps -> one launch: 17^3 9.5 -> 5.2 us, 33^3 9.4 -> 6.9 us.
-#include "sbm_internal.h"
+#include "sbm_tile.h"
 
 namespace sbm {
 namespace {
@@ -139,12 +139,8 @@ hipError_t launch_sweep3(const Level &L, const double *xin, const double *f, dou
   const int ntx = (L.g.nx + BX - 1) / BX, nty = (L.g.ny + BY - 1) / BY;
   const int n = ntx * nty * ((L.g.nz + BZ - 1) / BZ);
   const Coef<double> &C = L.c64;
-  const CoefCubic<double> cc{C.cd[0][0], C.cd[0][1], C.cp[0], C.cm[0]};
-  bool cubic = true;
-  for (int i = 0; i < 3; ++i) {
-    cubic = cubic && C.cp[i] == cc.p && C.cm[i] == cc.m;
-    for (int j = 0; j < 3; ++j) cubic = cubic && C.cd[i][j] == (i == j ? cc.dd : cc.od);
-  }
+  CoefCubic<double> cc;
+  const bool cubic = cubic_coef(C, cc);
   (void)hipGetLastError();
   const dim3 grid((n + 7) / 8 * 8), block(NT3);
   if (cubic)
