@@ -305,14 +305,14 @@ hipError_t launch_leg2_up(const Level &L, const Level &Lc, const double *xin, co
                           double *xout, const double *e, double omega, int first_colour, int nu,
                           hipStream_t st);
 // The inverse of the bottom operator ((DOF)^2 values), a column per workgroup by
-// the bottom CG to an updated residual of tol; state (two ints, 0 on entry): [1] is set
+// the bottom CG to an updated residual of tol; state (three ints, 0 on entry): [1] is set
 // when a column's own residual is too large to refine; [0] is the caller's, nonzero
 // where cycles are to use it.
 hipError_t launch_bottom_inverse(const Level &B, double *inv, int *state, double tol, int maxit,
                                  hipStream_t st);
 // x = inv f, refined once unless its residual is that of a solve to rtol, where the
 // state says that inv is in use (y: scratch of the bottom's size).
-hipError_t launch_bottom_product(const Level &B, const double *inv, const int *state, double rtol,
+hipError_t launch_bottom_product(const Level &B, const double *inv, int *state, double rtol,
                                  const double *f, double *y, double *x, hipStream_t st);
 template <typename T>
 hipError_t launch_tail(int dim, bool wide_bottom, const void *dev, size_t lds_bytes,

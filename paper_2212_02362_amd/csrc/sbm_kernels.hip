@@ -1139,7 +1139,8 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom_cg(Geom g, Coef<T> C,
 
 // FP64 bottom: x += CG solution of K_FF d = (f - K x)_F.  f and x are FP64,
 // or FP32 in the mixed cycle (read into and written from the FP64 solve).  Where the
-// state says that the inverse made x, only its residual is looked at (bottom_solved).
+// state says that the inverse made x, its residual is looked at (bottom_solved) unless
+// it has been.
 template <int DIM, int Q, typename IO>
 __global__ __launch_bounds__(kBotThreads) void k_bottom_lds64(Geom g, Coef<double> C,
                                                        const double *__restrict__ psi,
@@ -1148,6 +1149,11 @@ __global__ __launch_bounds__(kBotThreads) void k_bottom_lds64(Geom g, Coef<doubl
                                                        const int *inv_state) {
   extern __shared__ double smem[];
   __shared__ double red[64];
+  const bool inverse = inv_state && inv_state[0] != 0 && inv_state[1] == 0;
+  if (inverse && inv_state[2] != 0) {  // x stands
+    if (threadIdx.x == 0 && iters) *iters = 1;
+    return;
+  }
   BotRed R{red, 0};
   const int64_t n = g.nn;
   double *psi_l = smem;
@@ -1192,7 +1198,7 @@ __global__ __launch_bounds__(kBotThreads) void k_bottom_lds64(Geom g, Coef<doubl
     }
   }
   __syncthreads();
-  if (inv_state && inv_state[0] != 0 && inv_state[1] == 0) {
+  if (inverse) {
     // x comes from the inverse: it stands, or the CG starts from zero
     bot_allsum3(sum, red);
     if (bottom_solved(sum, rtol)) {

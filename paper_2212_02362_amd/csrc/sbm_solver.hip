@@ -120,7 +120,7 @@ struct sbm_ctx {
   int tail64 = -1, tail32 = -1;
   char *tail_args = nullptr;
   double *tail_A = nullptr;  // dense bottom matrix of the tails
-  // inverse of the bottom operator (FP64 cycles), its state in iflag[13], [14]
+  // inverse of the bottom operator (FP64 cycles), its state in iflag[13] to [15]
   double *tail_inv = nullptr;
   bool inv_ready = false;  // formed for the current problem and options
   bool inv_on = false;     // iflag[13]: cycles use it
@@ -611,7 +611,7 @@ static bool inverse_ok(const sbm_ctx *c);
 // cycle: x is 0 on entry (the inverse may stand for the CG, if its residual does).
 static hipError_t bottom64(sbm_ctx *c, const double *f, double *x, bool cycle) {
   Level &B = c->L[c->nlev - 1];
-  const int *state = cycle && inverse_ok(c) ? c->iflag + 13 : nullptr;
+  int *state = cycle && inverse_ok(c) ? c->iflag + 13 : nullptr;
   hipError_t e;
   if (state && (e = launch_bottom_product(B, c->tail_inv, state, c->opt.bottom_rtol, f, c->b_r, x,
                                           c->st)) != hipSuccess)
@@ -639,10 +639,11 @@ static bool inverse_ok(const sbm_ctx *c) {
 }
 
 // Cycles that a solve has to have left for the inverse to pay.  Forming it is as many CG
-// solves as DOF side by side: up to 512 DOF little more than one CG (112 nodes: 247
-// against 215 us), above a few (28^3 cells, 512 nodes: 2.8 ms against 0.63 ms per cycle).
+// solves as DOF side by side, a workgroup each: little more than one CG while they fit the
+// CUs, then in proportion (336 DOF 247 us, the CG of a cycle 215 us; 672 DOF 277 / 167 us;
+// 1536 DOF 2750 / 565 us).
 static int inverse_pays(const sbm_ctx *c) {
-  return c->dim * c->L.back().g.nn <= kTailInverse ? 2 : 6;
+  return 2 + (int)(c->dim * c->L.back().g.nn) / 384;
 }
 
 double sbm::cycles_left(double rho, double before, double rtol, int m, int max_cycles) {
@@ -1314,7 +1315,7 @@ sbm_status sbm_set_options(sbm_ctx *c, const sbm_options *opts) {
     HIP_TRY(hipStreamSynchronize(c->st));
     drop_graphs(c);
     c->inv_ready = c->inv_on = false;
-    HIP_TRY(launch_fill<int>(c->iflag + 13, 2, 0, c->st));
+    HIP_TRY(launch_fill<int>(c->iflag + 13, 3, 0, c->st));
   }
   c->opt = *opts;
   return SBM_OK;

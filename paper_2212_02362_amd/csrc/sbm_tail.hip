@@ -60,7 +60,7 @@ struct TailArgs {
 static_assert(sizeof(TailArgs<double>) <= kTailArgBytes, "tail table too large");
 
 // The state of the bottom's inverse: [0] it is formed and in use, [1] a column is too
-// far off to refine with.
+// far off to refine with, [2] (outside the tail) the last product stands unrefined.
 __device__ __forceinline__ bool inverse_there(const int *state) {
   return state[0] != 0 && state[1] == 0;
 }
@@ -450,7 +450,8 @@ struct Tail {
   // the row, the parts are added in order; then the residual, and up to kTailRefine
   // steps of refinement.  Returns whether that solves it; else the CG does.  It takes
   // the place of a CG of some n3 dependent iterations of 1 to 2 us (bound by
-  // latency).  Bound by reading n3^2 values from L2.
+  // latency).  Bound by reading n3^2 values from L2; the whole tail with a bottom of
+  // 112 nodes 259 -> 59 us, of 27 nodes 59 -> 50 us (the residual 4 to 8 us of it).
   __device__ __forceinline__ bool bottom_inverse(int *iters) const {
     const int n3 = a.n3, n = (int)a.gb.nn, pitch = (n3 + 63) & ~63;
     const int s = threadIdx.x / pitch, i = threadIdx.x - s * pitch;
@@ -680,7 +681,7 @@ __global__ __launch_bounds__(64) void k_tail_assemble(const TailArgs<T> *__restr
 
 // Column b of the bottom's inverse: the bottom CG for the unit vector of DOF b,
 // a workgroup each (112 nodes: 336 columns side by side 247 us, one CG 215 us; 27
-// nodes 43 us; 512 nodes: 1536 columns 1530 us, one CG 420 us).
+// nodes 43 us; 512 nodes: 1536 columns 2750 us, one CG 565 us).
 template <int DIM>
 __global__ __launch_bounds__(kTailThreads) void k_bottom_inverse(
     Geom g, Coef<double> C, const double *__restrict__ psib, double *__restrict__ inv,
@@ -733,9 +734,9 @@ __global__ __launch_bounds__(kTailThreads) void k_bottom_inverse(
 // y = inverse f for a bottom outside the tail (the tail holds two levels or more
 // in LDS): 64 rows per workgroup, a wave per sixteenth of their sums.  Then x = y, or
 // the refined y + inverse (f - K y) where the residual of y is not that of a solve
-// (every workgroup forms it); the bottom kernel launched behind looks at that of x.
+// (every workgroup forms it), and the bottom kernel launched behind looks at that of x.
 // Without an inverse both leave x as it is.  Bound by the latency of n3 / 16 loads in
-// flight 16 at a time.
+// flight 16 at a time (512 nodes: product 24 us, residual 10 us; CG 565 us).
 constexpr int kProdParts = 16;
 __device__ __forceinline__ double product_row(int n3, const double *__restrict__ inv,
                                               const double *f, double (*part)[64]) {
@@ -763,7 +764,7 @@ __global__ __launch_bounds__(64 * kProdParts) void k_bottom_product(
 template <int DIM>
 __global__ __launch_bounds__(64 * kProdParts) void k_bottom_refine(
     Geom g, Coef<double> C, const double *__restrict__ psi, const double *__restrict__ inv,
-    const int *__restrict__ state, double rtol, const double *__restrict__ f,
+    int *__restrict__ state, double rtol, const double *__restrict__ f,
     const double *__restrict__ y, double *__restrict__ x) {
   __shared__ double part[kProdParts][64];
   __shared__ double rl[DIM * kInverseNodes];
@@ -777,7 +778,9 @@ __global__ __launch_bounds__(64 * kProdParts) void k_bottom_refine(
     for (int c = 0; c < DIM; ++c) rl[c * n + threadIdx.x] = rv[c];
   }
   bot_allsum3(sum, red);
-  const double v = bottom_solved(sum, rtol) ? 0.0 : product_row(n3, inv, rl, part);
+  const bool solved = bottom_solved(sum, rtol);
+  const double v = solved ? 0.0 : product_row(n3, inv, rl, part);
+  if (blockIdx.x == 0 && threadIdx.x == 0) state[2] = solved ? 1 : 0;
   const int i = blockIdx.x * 64 + threadIdx.x;
   if (threadIdx.x < 64 && i < n3) x[i] = y[i] + v;
 }
@@ -926,7 +929,7 @@ hipError_t launch_bottom_inverse(const Level &B, double *inv, int *state, double
   return hipGetLastError();
 }
 
-hipError_t launch_bottom_product(const Level &B, const double *inv, const int *state, double rtol,
+hipError_t launch_bottom_product(const Level &B, const double *inv, int *state, double rtol,
                                  const double *f, double *y, double *x, hipStream_t st) {
   const int n = (int)B.g.nn, n3 = B.g.dim * n;
   if (n > kInverseNodes) return hipErrorInvalidValue;
