@@ -657,41 +657,35 @@ def _kernel_hash(files=("sbm_device.h", "sbm_kernels.hip")):
     return h.hexdigest()[:16]
 
 
-def _traffic(kernel_key, nodes):
-    """HBM bytes per launch from the committed rocprofv3 counter summary, if it
-    was taken on the current kernel sources; else None."""
+def _traffic(nodes):
+    """HBM bytes per launch of the FP64 half-sweep on split rows from the committed
+    rocprofv3 counter summary, if it was taken on the current kernel sources at this
+    size; else None."""
     path = os.path.join(ROOT, "profiles", "traffic_counters.json")
     if not os.path.exists(path):
         return None
     with open(path) as fh:
         data = json.load(fh)
-    ent = data.get(kernel_key)
-    files = next((v[2] for v in COUNTER_KERNELS.values() if v[0] == kernel_key), None)
-    if not ent or files is None or ent.get("kernel_hash") != _kernel_hash(files) or \
-            ent.get("nodes") != nodes:
+    ent = next((e for e in data.values() if e.get("nodes") == nodes), None)
+    if not ent or ent.get("kernel_hash") != _kernel_hash(COUNTER_SOURCES):
         return None
     return ent.get("hbm_bytes_per_launch")
 
 
-TRAFFIC_KERNEL = "k_rb_half<double,3,false>"
-# counter runs per workload: (key in traffic_counters.json, kernel name in the
-# rocprofv3 trace, the sources whose hash keys the entry).  The 129^3 vectors
+# counter runs per workload: the key in traffic_counters.json.  The 129^3 vectors
 # fit the 256 MB Infinity Cache; the 257^3 ones do not.
-COUNTER_KERNELS = {
-    "spherical_voids_129": (TRAFFIC_KERNEL, "k_rb_half<double, 3, false>",
-                            ("sbm_device.h", "sbm_kernels.hip")),
-    "diffuse_crack_257": ("k_rb_tile<double,false>",
-                          "k_rb_tile<double, sbm::CoefCubic<double>, false, false>",
-                          ("sbm_device.h", "sbm_tiled.hip")),
-}
+COUNTER_KERNELS = {w: "k_rb_split<double> " + w
+                   for w in ("spherical_voids_129", "diffuse_crack_257")}
+COUNTER_TRACE = "k_rb_split<double, sbm::CoefCubic<double>, 0>"  # in the rocprofv3 trace
+COUNTER_SOURCES = ("sbm_device.h", "sbm_tile.h", "sbm_split.hip")
 COPY_BYTES = 400_000_000  # calibration copy: this many bytes read and written
 
 
 def _counter_driver(workload="spherical_voids_129"):
-    """Workload for the two rocprofv3 counter passes: the finest-level
-    half-sweep of the workload, launched as inside its V-cycles (same kernel,
-    level and launch shape), then a plain device copy of known size that
-    calibrates FETCH_SIZE / WRITE_SIZE."""
+    """Workload for the two rocprofv3 counter passes: four CG iterations launched kernel
+    by kernel, with 25 plain half-sweeps of the finest level (the launches of the largest
+    grid), then a plain device copy of known size that calibrates FETCH_SIZE /
+    WRITE_SIZE."""
     import torch
 
     from paper_2212_02362_amd import Solver
@@ -699,19 +693,9 @@ def _counter_driver(workload="spherical_voids_129"):
     if workload not in COUNTER_KERNELS:
         raise SystemExit(f"no counter run defined for {workload}")
     p, _ = _workload(workload)
-    S = Solver(p.ncell, p.h)
+    S = Solver(p.ncell, p.h, krylov=1, rtol=0.0, max_cycles=4, use_graphs=0)
     S.set_problem(torch.tensor(p.psi_raw, device="cuda"), p.lam, p.mu, p.psi_floor, p.kind, p.val)
-    import ctypes
-
-    from paper_2212_02362_amd._lib import check, lib
-    u = torch.randn((p.dim,) + p.node_shape, dtype=torch.float64, device="cuda")
-    f = torch.randn_like(u)
-    v = torch.empty_like(u)
-    ptr = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
-    # ping-pong between two resident buffers, as the V-cycle does
-    for it in range(10):
-        check(lib().sbm_level_smooth(S._ctx, 0, it % 2, 1.0, ptr(u), ptr(f), ptr(v)))
-        u, v = v, u
+    S.solve()
     x = torch.randn(COPY_BYTES // 8, dtype=torch.float64, device="cuda")
     y = torch.empty_like(x)
     for _ in range(3):
@@ -729,7 +713,7 @@ def _counter_summary(fetch_dir, write_dir, workload="spherical_voids_129"):
 
     if workload not in COUNTER_KERNELS:
         raise SystemExit(f"no counter run defined for {workload}")
-    key, trace_name, files = COUNTER_KERNELS[workload]
+    key = COUNTER_KERNELS[workload]
 
     def read(d, counter):
         path = None
@@ -739,20 +723,21 @@ def _counter_summary(fetch_dir, write_dir, workload="spherical_voids_129"):
                     path = os.path.join(root, fn)
         if path is None:
             raise SystemExit(f"no counter_collection.csv under {d}")
-        kern, copy = [], []
+        kern, copy = {}, []
         with open(path) as fh:
             for r in csv.DictReader(fh):
                 if r["Counter_Name"] != counter:
                     continue
                 v = float(r["Counter_Value"]) * 1024.0  # KiB -> bytes
                 name = r["Kernel_Name"]
-                if trace_name in name:
-                    kern.append(v)
+                if COUNTER_TRACE in name:
+                    kern.setdefault(int(r["Grid_Size"]), []).append(v)
                 elif "copyBuffer" in name and v > 0.25 * COPY_BYTES:
                     copy.append(v)
         if not kern or not copy:
             raise SystemExit(f"{counter}: kernel or calibration copy missing in {path}")
-        return sum(kern) / len(kern), sum(copy) / len(copy), len(kern)
+        finest = kern[max(kern)]
+        return sum(finest) / len(finest), sum(copy) / len(copy), len(finest)
 
     fk, fc, nf = read(fetch_dir, "FETCH_SIZE")
     wk, wc, nw = read(write_dir, "WRITE_SIZE")
@@ -760,11 +745,11 @@ def _counter_summary(fetch_dir, write_dir, workload="spherical_voids_129"):
     p, _ = _workload(workload)
     nodes = p.n_nodes
     fetch, write = fk * ff, wk * fw
-    ent = {"kernel_hash": _kernel_hash(files), "nodes": nodes, "workload": workload,
+    ent = {"kernel_hash": _kernel_hash(COUNTER_SOURCES), "nodes": nodes, "workload": workload,
            "hbm_bytes_per_launch": fetch + write,
            "fetch_bytes_per_launch": fetch, "write_bytes_per_launch": write,
            "fetch_factor": ff, "write_factor": fw, "launches": [nf, nw],
-           "algo_bytes_per_launch": ALGO_BYTES["smooth"][0] * nodes}
+           "algo_bytes_per_launch": SPLIT_BYTES["smooth"][0] * nodes}
     path = os.path.join(ROOT, "profiles", "traffic_counters.json")
     data = {}
     if os.path.exists(path):
@@ -970,7 +955,7 @@ def main():
     avg_ms = ms_s / max(n_s, 1)
     by = (SPLIT_BYTES if split64 else ALGO_BYTES)["smooth"][0] * nodes
     achieved = by / (avg_ms * 1e-3) / 1e9
-    traffic = None if split64 else _traffic(TRAFFIC_KERNEL, nodes)
+    traffic = _traffic(nodes) if split64 else None
     line = {
         "metric": METRIC,
         "value": free / t64,
